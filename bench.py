@@ -38,7 +38,7 @@ PEAK_HBM = 8.0e12        # bytes/s
 # Sources of the pair-transform kernel (device code and its launch shapes);
 # HBM traffic figures taken with rocprofv3 counters are only reported while
 # these are unchanged.
-PAIR_SOURCES = ("fft.hpp", "transforms.hpp", "kernels_fft.hpp", "grid_kernels.hip")
+PAIR_SOURCES = ("fft.hpp", "rfft.hpp", "kernels_pair.hpp", "grid_kernels.hip")
 COPY_PROBE_BYTES = 1 << 30
 
 

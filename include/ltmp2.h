@@ -454,8 +454,10 @@ ltmp2_status ltmp2_batch_info(const ltmp2_batch* b, ltmp2_batch_stats* stats);
  * eagerly (not from the captured graph) so that launches can be bracketed. */
 ltmp2_status ltmp2_batch_set_timing(ltmp2_batch* b, int on);
 ltmp2_status ltmp2_batch_get_timing(ltmp2_batch* b, int stage, double* ms, long* launches);
-/* Group g: grid size, cells, rounds of outer G', tuned slab tile and
- * workgroups per CU of the fused pair launch, tuned launch time (ms). */
+/* Group g: grid size, cells, rounds of outer G', and the shape of its largest
+ * fused pair launch: x planes whose lines one round of a workgroup covers,
+ * workgroups resident on a CU (4: four or more).  The shape is fixed by the
+ * grid and the kept set, nothing is timed: tuned_ms is 0. */
 ltmp2_status ltmp2_batch_group(const ltmp2_batch* b, int g, int* n_fft, int* n_cells, int* rounds,
                                int* slab_tile, int* wg_per_cu, double* tuned_ms);
 ltmp2_status ltmp2_batch_cell(const ltmp2_batch* b, int k, ltmp2_info* info);

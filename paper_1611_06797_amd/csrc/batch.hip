@@ -7,12 +7,10 @@
 //    products P, transformed states w) is pooled across cells.
 //  * Within a group, the outer G' loop of every cell is cut into the same
 //    number of rounds.  For each Laplace point and round, every active cell
-//    runs its transformed-state GEMM and synthesis, then ONE persistent fused
-//    launch evaluates the Fock-like pair transforms of all cells of the group
-//    (descriptor table + prefix sums over the cells' work lists).
-//  * A tuner picks, per group, the slab tile of the pair transform and the
-//    number of resident workgroups per CU of the persistent launch by timing
-//    the candidates once; choices are cached per (grid, precision).
+//    runs its transformed-state GEMM and synthesis, then ONE fused launch per
+//    kept-set instance evaluates the Fock-like pair transforms of all cells of
+//    the group (descriptor table + prefix sums over the cells' work lists, one
+//    workgroup per item).
 //  * The whole launch sequence is captured into a hipGraph after the first
 //    (eager) evaluation and replayed by later calls.
 #include <hip/hip_runtime.h>
@@ -20,9 +18,7 @@
 #include <algorithm>
 #include <cmath>
 #include <map>
-#include <mutex>
 #include <string>
-#include <tuple>
 #include <vector>
 
 #include "../../include/ltmp2.h"
@@ -39,40 +35,20 @@ struct Part {
   PairCell* d_cells = nullptr;
   long* d_prefix = nullptr;
   long total = 0;
-  int ng_max = 0, kmax_max = 0, kfix = -1;
+  int kmax_max = 0, ncol_max = 0;
 };
 using Round = std::vector<Part>;
-
-int round_kmax(const Round& r) {
-  int k = 0;
-  for (const Part& p : r) k = std::max(k, p.kmax_max);
-  return k;
-}
-
-int sched_kmax(const std::vector<std::vector<Round>>& sched) {
-  int k = 0;
-  for (const auto& rounds : sched)
-    for (const Round& r : rounds) k = std::max(k, round_kmax(r));
-  return k;
-}
 
 struct Group {
   int n = 0;
   std::vector<int> cells;
   int rounds = 1;
-  int sx = 1, wg_per_cu = 2;
+  int planes = 1, wg_per_cu = 1;  // launch shape (ltmp2_batch_group)
   int max_ntau = 0;
   std::vector<std::vector<Round>> sched;  // [itau][round]
-  double tuned_ms = 0.0;
-  bool tuned = false;
 };
 
 thread_local std::string g_batch_error;
-
-std::mutex g_tune_mu;
-// (n, prec, largest kept set of the group) -> (sx, wg/CU): the slab tile that
-// fits shared memory depends on the kept set, so it is part of the key
-std::map<std::tuple<int, int, int>, std::pair<int, int>> g_tune_cache;
 
 }  // namespace
 
@@ -90,7 +66,6 @@ struct ltmp2_batch {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   long calls = 0;
-  int num_cus = 256;
   // optional event timing of the fused pair launches (eager evaluation only)
   bool timing = false;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> marks;
@@ -123,23 +98,20 @@ ltmp2_status balloc(ltmp2_batch* b, void** p, size_t bytes) {
 }
 
 template <class T>
-ltmp2_status fused_pair(ltmp2_batch* b, const Group& g, const Part& r, int sx, int wg) {
+ltmp2_status fused_pair(ltmp2_batch* b, const Group& g, const Part& r) {
   if (r.total == 0) return LTMP2_OK;
-  const GridOps<T>* ops = grid_ops<T>(g.n);
-  long nblk = std::min<long>((r.total + 7) / 8 * 8, long(wg) * b->num_cus);
-  nblk = std::max<long>(8, nblk / 8 * 8);
-  return ops->pair_multi(r.d_cells, r.d_prefix, int(r.cells.size()), r.ng_max, r.kmax_max,
-                         r.kfix, sx, int(nblk), b->stream);
+  return grid_ops<T>(g.n)->pair_multi(r.d_cells, r.d_prefix, int(r.cells.size()), r.total,
+                                      r.kmax_max, r.ncol_max, b->stream);
 }
 
-ltmp2_status pair_launch(ltmp2_batch* b, const Group& g, const Round& rd, int sx, int wg) {
+ltmp2_status pair_launch(ltmp2_batch* b, const Group& g, const Round& rd) {
   for (const Part& r : rd) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (b->timing && r.total > 0 && hipEventCreate(&e0) == hipSuccess &&
         hipEventCreate(&e1) == hipSuccess)
       (void)hipEventRecord(e0, b->stream);
-    const ltmp2_status s = b->prec == LTMP2_FP64 ? fused_pair<double>(b, g, r, sx, wg)
-                                                 : fused_pair<float>(b, g, r, sx, wg);
+    const ltmp2_status s = b->prec == LTMP2_FP64 ? fused_pair<double>(b, g, r)
+                                                 : fused_pair<float>(b, g, r);
     if (e1) {
       (void)hipEventRecord(e1, b->stream);
       b->marks.push_back({e0, e1});
@@ -185,7 +157,7 @@ ltmp2_status run_group(ltmp2_batch* b, const Group& g) {
         if ((s = exchange_block_prepare(c, it, g0, gb)))
           return bfail(b, s, "cell transformed states: " + c->err);
       }
-      if ((s = pair_launch(b, g, g.sched[it][r], g.sx, g.wg_per_cu)))
+      if ((s = pair_launch(b, g, g.sched[it][r])))
         return bfail(b, s, "fused pair launch failed");
     }
     for (int ci : g.cells) {
@@ -202,63 +174,6 @@ ltmp2_status run_all(ltmp2_batch* b) {
     ltmp2_status s = run_group(b, g);
     if (s) return s;
   }
-  return LTMP2_OK;
-}
-
-// Time the fused pair launch of (tau 0, round 0) for each candidate tile.
-ltmp2_status tune_group(ltmp2_batch* b, Group& g) {
-  const int kmax_g = sched_kmax(g.sched);
-  const std::tuple<int, int, int> key{g.n, b->prec, kmax_g};
-  {
-    std::lock_guard<std::mutex> lk(g_tune_mu);
-    auto it = g_tune_cache.find(key);
-    if (it != g_tune_cache.end()) {
-      g.sx = it->second.first;
-      g.wg_per_cu = it->second.second;
-      g.tuned = true;
-      return LTMP2_OK;
-    }
-  }
-  const Round& r0 = g.sched[0][0];
-  ltmp2_status s;
-  for (int ci : g.cells) {
-    ltmp2_ctx* c = b->cells[ci];
-    const int gb = std::min(c->gblock, c->nh);
-    if ((s = exchange_block_prepare(c, 0, 0, gb))) return bfail(b, s, "tuning prepare: " + c->err);
-  }
-  // every round of the group must fit the chosen tile
-  const int smax = b->prec == LTMP2_FP64 ? grid_ops<double>(g.n)->pair_sx_max(kmax_g)
-                                         : grid_ops<float>(g.n)->pair_sx_max(kmax_g);
-  std::vector<int> sxs{smax};
-  if (smax > 1) sxs.push_back(slab_tile_at_most(g.n, smax - 1));
-  hipEvent_t e0, e1;
-  if (hipEventCreate(&e0) || hipEventCreate(&e1)) return bfail(b, LTMP2_EDEVICE, "event");
-  double best = 1e300;
-  int bsx = smax, bwg = 2;
-  for (int sx : sxs)
-    for (int wg : {1, 2, 3, 4}) {
-      if ((s = pair_launch(b, g, r0, sx, wg))) break;  // warm-up of this variant
-      (void)hipEventRecord(e0, b->stream);
-      if ((s = pair_launch(b, g, r0, sx, wg))) break;
-      (void)hipEventRecord(e1, b->stream);
-      (void)hipEventSynchronize(e1);
-      float ms = 0.f;
-      (void)hipEventElapsedTime(&ms, e0, e1);
-      if (ms < best) {
-        best = ms;
-        bsx = sx;
-        bwg = wg;
-      }
-    }
-  (void)hipEventDestroy(e0);
-  (void)hipEventDestroy(e1);
-  if (s) return bfail(b, s, "tuning launch failed");
-  g.sx = bsx;
-  g.wg_per_cu = bwg;
-  g.tuned_ms = best;
-  g.tuned = true;
-  std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_tune_cache[key] = {bsx, bwg};
   return LTMP2_OK;
 }
 
@@ -298,12 +213,6 @@ extern "C" ltmp2_status ltmp2_batch_create(int n_cells, const ltmp2_params* para
     b->own_stream = true;
   }
   b->prec = prec;
-  int dev = 0;
-  if (hipGetDevice(&dev) == hipSuccess) {
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, dev) == hipSuccess && prop.multiProcessorCount > 0)
-      b->num_cus = prop.multiProcessorCount;
-  }
   // per-cell preparation without private scratch
   for (int k = 0; k < n_cells; ++k) {
     ltmp2_ctx* c = new ltmp2_ctx();
@@ -385,18 +294,15 @@ extern "C" ltmp2_status ltmp2_batch_create(int n_cells, const ltmp2_params* para
         }
         for (auto& kv : by_kept) {
           Part rd;
-          rd.kfix = kv.first;
           std::vector<long> prefix{0};
           for (int ci : kv.second) {
             ltmp2_ctx* c = b->cells[ci];
             const int g0 = r * c->gblock;
             const int gb = std::min(c->gblock, c->nh - g0);
-            rd.cells.push_back(PairCell{c->d_psi, c->d_w, c->d_pairs, c->d_gdesc, c->d_v,
-                                        c->d_xpart + size_t(g0) * c->npairs, c->nrp, c->no,
-                                        c->npairs, gb, c->ng, c->kmax_aux, c->dV * c->dV});
+            rd.cells.push_back(pair_cell(c, g0, gb));
             prefix.push_back(prefix.back() + long(c->npairs) * gb);
-            rd.ng_max = std::max(rd.ng_max, c->ng);
             rd.kmax_max = std::max(rd.kmax_max, c->kmax_aux);
+            rd.ncol_max = std::max(rd.ncol_max, c->ncol);
           }
           rd.total = prefix.back();
           void *pc = nullptr, *pp = nullptr;
@@ -416,10 +322,18 @@ extern "C" ltmp2_status ltmp2_batch_create(int n_cells, const ltmp2_params* para
           g.sched[it][r].push_back(std::move(rd));
         }
       }
-    // largest slab tile allowed by shared memory for this group
-    const int km = sched_kmax(g.sched);
-    g.sx = b->prec == LTMP2_FP64 ? grid_ops<double>(g.n)->pair_sx_max(km)
-                                 : grid_ops<float>(g.n)->pair_sx_max(km);
+    // launch shape of the group's largest launch
+    const Part* big = nullptr;
+    for (const auto& rounds : g.sched)
+      for (const Round& r : rounds)
+        for (const Part& p : r)
+          if (!big || p.total > big->total) big = &p;
+    if (big) {
+      if (b->prec == LTMP2_FP64)
+        grid_ops<double>(g.n)->pair_shape(big->kmax_max, big->ncol_max, &g.planes, &g.wg_per_cu);
+      else
+        grid_ops<float>(g.n)->pair_shape(big->kmax_max, big->ncol_max, &g.planes, &g.wg_per_cu);
+    }
   }
   *out = b;
   return LTMP2_OK;
@@ -431,8 +345,6 @@ extern "C" ltmp2_status ltmp2_batch_energy(ltmp2_batch* b, double* e_direct,
   if (b->failed) return bfail(b, LTMP2_ESTATE, "batch failed earlier: " + b->err);
   ltmp2_status s;
   if (b->calls == 0 || b->timing) {
-    for (Group& g : b->groups)
-      if (!g.tuned && (s = tune_group(b, g))) return s;
     if ((s = run_all(b))) return s;  // eager evaluation (first call, or timed)
   } else {
     if (!b->exec) {
@@ -525,9 +437,9 @@ extern "C" ltmp2_status ltmp2_batch_group(const ltmp2_batch* b, int g, int* n_ff
   if (n_fft) *n_fft = G.n;
   if (n_cells) *n_cells = int(G.cells.size());
   if (rounds) *rounds = G.rounds;
-  if (slab_tile) *slab_tile = G.sx;
-  if (wg_per_cu) *wg_per_cu = G.wg_per_cu;
-  if (tuned_ms) *tuned_ms = G.tuned_ms;
+  if (slab_tile) *slab_tile = G.planes;
+  if (wg_per_cu) *wg_per_cu = std::min(4, G.wg_per_cu);
+  if (tuned_ms) *tuned_ms = 0.0;
   return LTMP2_OK;
 }
 

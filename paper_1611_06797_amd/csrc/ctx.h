@@ -46,6 +46,10 @@ struct ltmp2_ctx {
   signed char* d_wsgn = nullptr;
   int* d_gdesc = nullptr;
   int* d_pairs = nullptr;
+  int* d_cols = nullptr;          // [ncol] columns of the pair transforms (PairCell)
+  double* d_vm2 = nullptr;        // [nm2] v(G) by m^2
+  signed char* d_shm2 = nullptr;  // [nm2] spheres by m^2 (cutoff extrapolation)
+  int ncol = 0, nm2 = 0;
   double* d_v = nullptr;
   double* d_fo = nullptr;  // [ntau][no]
   double* d_fv = nullptr;  // [ntau][nv]
@@ -53,13 +57,14 @@ struct ltmp2_ctx {
   // device data, element type double (FP64) or float (FP32, BF16X3)
   size_t esz = sizeof(double);
   void* d_psi = nullptr;       // [nst][nrp]
+  void* d_psiz = nullptr;      // [no][nrp] occupied, in the plane order of the pair transforms
   void* d_nd = nullptr;        // [nv][nh][no] complex
   void* d_bpw = nullptr;       // [nv][ldbpw] real basis of virtual coefficients
   void* d_chi = nullptr;       // [nrp][nrp]
   void* d_chihat = nullptr;    // [nh][nrp] complex
   double* d_pd = nullptr;      // [nh]
   void* d_P = nullptr;         // [gblock * no * 2][npw]
-  void* d_w = nullptr;         // [gblock * no][nrp] complex
+  void* d_w = nullptr;         // [gblock * no][2][nrp] real and imaginary fields, plane order
   double* d_xpart = nullptr;   // [nh][npairs]
   double* d_xrow = nullptr;    // [nh] v(G') times the row sums of d_xpart
   double* d_scal = nullptr;    // [2 * ntau + 8] device scalars
@@ -99,6 +104,7 @@ namespace ltmp2 {
 ltmp2_status run_direct(ltmp2_ctx* c, int itau, double* chi_out);
 ltmp2_status run_exchange(ltmp2_ctx* c, int itau, int g_first, int g_count);
 // Pieces of run_exchange used by batched execution.
+PairCell pair_cell(const ltmp2_ctx* c, int g0, int gb);
 ltmp2_status exchange_block_prepare(ltmp2_ctx* c, int itau, int g0, int gb);
 ltmp2_status exchange_reduce(ltmp2_ctx* c, int itau, int g_first, int g_count);
 ltmp2_status setup_cell(ltmp2_ctx* c, const int32_t* miller, const double* eps,

@@ -7,6 +7,7 @@
 
 #include "../../include/ltmp2.h"
 #include "kernels_fft.hpp"
+#include "kernels_pair.hpp"
 #include "modes.h"
 
 namespace ltmp2 {
@@ -30,22 +31,22 @@ struct GridOps {
                            const double* v, int kmax, double dV, double* pd,
                            cplx<double>* chi_out, ShellBins bins, hipStream_t st);
   ltmp2_status (*wstates)(const T* P, int npw, const int* wq, const signed char* wsgn,
-                          SphereCols sc, int nitems, double scale, cplx<T>* w, long ld,
+                          SphereCols sc, int nitems, double scale, T* w, long ld,
                           hipStream_t st);
-  // shell / xbins / nb / g0: optional split by auxiliary cutoff shell (PairCell)
-  ltmp2_status (*pair)(const T* psi, long ld, const cplx<T>* w, int no, const int* pairs,
-                       int npairs, int gb, const int* gdesc, int ng, const double* v, int kmax,
-                       double dV2, double* xpart, const signed char* shell, double* xbins,
-                       int nb, int g0, hipStream_t st);
-  // persistent multi-cell pair launch (device arrays cells[ncells], prefix[ncells + 1]);
-  // all cells share the kept-set instance kfix (pair_kept)
-  ltmp2_status (*pair_multi)(const PairCell* cells, const long* prefix, int ncells, int ng_max,
-                             int kmax_max, int kfix, int sx, int nblocks, hipStream_t st);
+  // pair transforms of one block of outer vectors of a cell
+  ltmp2_status (*pair)(const PairCell& pc, hipStream_t st);
+  // the same for several cells of one kept-set instance (device arrays
+  // cells[ncells], prefix[ncells + 1] of `total` items)
+  ltmp2_status (*pair_multi)(const PairCell* cells, const long* prefix, int ncells, long total,
+                             int kmax_max, int ncol_max, hipStream_t st);
   // Hartree-like direct term of one block of outer G' from h (k_hartree)
   ltmp2_status (*hartree)(const cplx<T>* h, long ld, const int* gdesc, int ng, const double* v,
                           int kmax, double dV, int g0, int gb, double* pdh, hipStream_t st);
-  int (*pair_sx_max)(int kmax);
-  // kept-set instance of the pair kernels for a cell's kmax (or -1: runtime form)
+  // launch shape of the fused pair launch (ltmp2_batch_group)
+  void (*pair_shape)(int kmax, int ncol, int* planes, int* wg_per_cu);
+  // occupied orbitals into the plane order of the pair transforms
+  ltmp2_status (*plane_order)(const T* in, long ld, int nocc, T* out, hipStream_t st);
+  // kept-set instance of the pair kernels for a cell's kmax (-1: none)
   int (*pair_kept)(int kmax);
 };
 
@@ -78,7 +79,7 @@ ltmp2_status launch_mm3(const void* ahi, const void* alo, long lda, long am0, co
 
 // h^{(G')}(r) = sum_i psi_i(r) w_i^{(G')}(r) for a block of gb outer vectors
 template <class T>
-ltmp2_status launch_hsum(const T* psi, long ld, const cplx<T>* w, int no, long nr, int gb,
+ltmp2_status launch_hsum(const T* psi, long ld, const T* w, int no, long nr, int gb,
                          cplx<T>* h, hipStream_t st);
 
 // float -> double copy (diagnostic outputs of FP32 contexts)

@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "dispatch.h"
 
@@ -62,22 +63,6 @@ template <class K>
 ltmp2_status launch(K kern, dim3 grid, size_t lds, hipStream_t st, auto... args) {
   return launch_nt(kern, grid, kThreads, lds, st, args...);
 }
-
-// FP32 pair transforms with more than 9 outputs per thread: on grids whose
-// auxiliary window allows them (n >= 30) 256-thread workgroups with up to 17
-// outputs each, held to two waves per SIMD by their launch bounds, two
-// workgroups per CU (36 grid: 118 ns per item against 135 ns for the
-// 512-thread joint form below, stand-alone timing); above 17 x 256 outputs
-// the 512-thread form with at most 9 each.  (FP64 keeps 256 threads.)
-constexpr int kWideNT = 512, kWideOpt = 9;
-// The wide form transforms both fields of an item side by side in two slab
-// buffers (forward_pruned_joint): on the 36 grid with 12-plane slabs that is
-// 864 z lines, 504 y rows and 882 columns per slab group for the 512 threads
-// (one field at a time: 432, 252 and 441), with half the barriers; one
-// workgroup per CU either way (the registers bind first).  Measured 8 %
-// faster than single-field 18-plane slabs, 23 % faster than single-field
-// 12-plane slabs.
-constexpr int kNarrowNT = 192;
 
 template <template <int> class F>
 ltmp2_status by_opt(int nout, auto&&... a) {
@@ -177,7 +162,7 @@ ltmp2_status hartree(const cplx<T>* h, long ld, const int* gdesc, int ng, const 
 
 template <class T>
 ltmp2_status wstates(const T* P, int npw, const int* wq, const signed char* wsgn, SphereCols sc,
-                     int nitems, double scale, cplx<T>* w, long ld, hipStream_t st) {
+                     int nitems, double scale, T* w, long ld, hipStream_t st) {
   // the largest slab tile that lets four workgroups share a CU, unless two
   // workgroups per CU would allow more than twice that tile
   const int nk = 2 * sc.kmax + 1;
@@ -202,182 +187,83 @@ ltmp2_status wstates(const T* P, int npw, const int* wq, const signed char* wsgn
   return launch(k_wstates<T, N>, dim3(nitems), lds, st, P, npw, wq, wsgn, sc, sx, scale, w, ld);
 }
 
-// Kept-set instance of the pair kernels for a cell: kwin(N), kwin(N) - 1 or
-// the runtime form (-1).
-inline int pair_kfix(int kmax) {
-  return (kmax == kwin(N) || (kwin(N) > 1 && kmax == kwin(N) - 1)) ? kmax : -1;
+// Kept-set instance of the pair kernels for a cell (-1: none holds it).
+int pair_instance(int kmax) {
+  constexpr int kw = pair_kw(N), kf = pair_kf(N);
+  if (kw > 1 && kmax <= kw - 1) return kw - 1;
+  if (kmax <= kw) return kw;
+  return kmax <= kf ? kf : -1;
+}
+
+// fn(integral_constant<KM>) for the instance that holds kmax.
+template <class Fn>
+ltmp2_status with_instance(int kmax, Fn&& fn) {
+  constexpr int kw = pair_kw(N), kf = pair_kf(N);
+  const int k = pair_instance(kmax);
+  if constexpr (kw > 1)
+    if (k == kw - 1) return fn(std::integral_constant<int, kw - 1>{});
+  if (k == kw) return fn(std::integral_constant<int, kw>{});
+  if constexpr (kf > kw)
+    if (k == kf) return fn(std::integral_constant<int, kf>{});
+  return LTMP2_EINVAL;
+}
+
+template <class T, int KM>
+size_t pair_lds(int ncol) {
+  constexpr int ns = pair_slabs(sizeof(T), N, KM);
+  return pair_lds_bytes(sizeof(T), N, KM, ns, ncol);
 }
 
 // Launches that split by cutoff shell run an instance with that epilogue
-// compiled in; the others run one without it (fewer live registers; in FP32
-// single-buffer forms its z lines are read through buffer resources).
-template <class T, int NT, int OPT, int KM, bool JOINT, int MINW>
-ltmp2_status pair_go(const PairCell& pc, int sx, hipStream_t st) {
-  const long total = long(pc.npairs) * pc.gb;
-  const int nk = 2 * pc.kmax + 1;
-  const dim3 grid(unsigned((total + 7) / 8 * 8));
-  const size_t lds = JOINT ? fwd2_lds_bytes<T>(N, nk, sx) : fwd_lds_bytes<T>(N, nk, sx);
-  if (pc.shell)
-    return launch_nt(k_pair<T, N, OPT, NT, KM, JOINT, true, MINW>, grid, NT, lds, st, pc, sx);
-  return launch_nt(k_pair<T, N, OPT, NT, KM, JOINT, false, MINW>, grid, NT, lds, st, pc, sx);
-}
-
-template <class T, int NT, int OPT, bool JOINT = false, int MINW = 1>
-ltmp2_status pair_km(const PairCell& pc, int sx, hipStream_t st) {
-  constexpr int kw = kwin(N);
-  const int kf = pair_kfix(pc.kmax);
-  if (kf == kw) return pair_go<T, NT, OPT, kw, JOINT, MINW>(pc, sx, st);
-  if constexpr (kw > 1)
-    if (kf == kw - 1) return pair_go<T, NT, OPT, kw - 1, JOINT, MINW>(pc, sx, st);
-  return pair_go<T, NT, OPT, -1, JOINT, MINW>(pc, sx, st);
-}
-
-// Largest slab tile d <= cap whose single slab buffer fits `limit` bytes.
+// compiled in; the others run one without it (fewer live registers).
 template <class T>
-int choose_sx_fwd_within(int nk, int cap, size_t limit) {
-  int sx = slab_tile_at_most(N, cap);
-  while (sx > 1 && fwd_lds_bytes<T>(N, nk, sx) > limit) sx = slab_tile_at_most(N, sx - 1);
-  return sx;
+ltmp2_status pair(const PairCell& pc, hipStream_t st) {
+  return with_instance(pc.kmax, [&](auto km) -> ltmp2_status {
+    constexpr int KM = decltype(km)::value, NT = pair_threads(sizeof(T), N, KM);
+    if (pc.ncol < 1 || pc.ncol > pair_cols_max(KM) || pc.nm2 > 2 * KM * KM + 2 * KM + 1)
+      return LTMP2_EINVAL;
+    const long total = long(pc.npairs) * pc.gb;
+    const dim3 grid(unsigned((total + 7) / 8 * 8));
+    const size_t lds = pair_lds<T, KM>(pc.ncol);
+    if (pc.shm2) return launch_nt(k_pair<T, N, KM, true>, grid, NT, lds, st, pc);
+    return launch_nt(k_pair<T, N, KM, false>, grid, NT, lds, st, pc);
+  });
 }
 
-// Largest slab tile d <= cap whose two slab buffers (both fields of a pair
-// item side by side) fit the shared memory.
+// Several cells of one kept-set instance in one launch of `total` items.
 template <class T>
-int choose_sx_joint(int nk, int cap) {
-  int sx = slab_tile_at_most(N, cap);
-  while (sx > 1 && fwd2_lds_bytes<T>(N, nk, sx) > kLdsCap) sx = slab_tile_at_most(N, sx - 1);
-  return sx;
+ltmp2_status pair_multi(const PairCell* cells, const long* prefix, int ncells, long total,
+                        int kmax_max, int ncol_max, hipStream_t st) {
+  return with_instance(kmax_max, [&](auto km) -> ltmp2_status {
+    constexpr int KM = decltype(km)::value, NT = pair_threads(sizeof(T), N, KM);
+    if (ncol_max < 1 || ncol_max > pair_cols_max(KM)) return LTMP2_EINVAL;
+    const dim3 grid(unsigned((total + 7) / 8 * 8));
+    return launch_nt(k_pair_multi<T, N, KM>, grid, NT, pair_lds<T, KM>(ncol_max), st, cells,
+                     prefix, ncells);
+  });
 }
 
+// Launch shape of an instance: x planes whose z lines one round of a
+// workgroup covers, and workgroups resident on a CU.
 template <class T>
-struct PairF {
-  template <int OPT>
-  struct F {
-    static ltmp2_status go(const PairCell& pc, int sx, hipStream_t st) {
-      if constexpr (sizeof(T) == sizeof(float) && OPT > 9) {
-        return LTMP2_EINVAL;  // FP32 takes the 512-thread form above 9 outputs
-      } else {
-        return pair_km<T, kThreads, OPT>(pc, sx, st);
-      }
-    }
-  };
-};
-template <class T>
-ltmp2_status pair(const T* psi, long ld, const cplx<T>* w, int no, const int* pairs, int npairs,
-                  int gb, const int* gdesc, int ng, const double* v, int kmax, double dV2,
-                  double* xpart, const signed char* shell, double* xbins, int nb, int g0,
-                  hipStream_t st) {
-  PairCell pc{psi, w, pairs, gdesc, v, xpart, ld, no, npairs, gb, ng, kmax, dV2};
-  pc.shell = shell;
-  pc.xbins = xbins;
-  pc.nb = nb;
-  pc.g0 = g0;
-  if constexpr (sizeof(T) == sizeof(float)) {
-    if (ng > 9 * kThreads) {
-      // up to 17 outputs per thread: 256 threads with two waves per SIMD
-      // held by the launch bounds (244 registers, no spills on the 36 grid)
-      // and 12-plane slabs within half the shared memory, so two workgroups
-      // share a CU and overlap each other's barriers
-      // (compiled for the two fixed kept sets only: the runtime-kmax form
-      // spills at 256 registers and takes the 512-thread path instead)
-      if constexpr (kwin(N) >= 9) {
-        constexpr int kw = kwin(N);
-        const int kf = pair_kfix(kmax);
-        const int sx = choose_sx_fwd_within<T>(2 * kmax + 1, 12, kLdsHalf);
-        if (ng <= 17 * kThreads && kf == kw)
-          return pair_go<T, kThreads, 17, kw, false, 2>(pc, sx, st);
-        if (ng <= 17 * kThreads && kf == kw - 1)
-          return pair_go<T, kThreads, 17, kw - 1, false, 2>(pc, sx, st);
-      }
-      if (ng > kWideOpt * kWideNT) return LTMP2_EINVAL;
-      return pair_km<T, kWideNT, kWideOpt, true>(pc, choose_sx_joint<T>(2 * kmax + 1, 12), st);
-    }
-  }
-  return by_opt<PairF<T>::template F>(ng, pc, choose_sx_fwd<T>(2 * kmax + 1), st);
-}
-
-template <class T, int NT, int OPT, int KM, int MINW = 1>
-ltmp2_status pair_multi_go(const PairCell* cells, const long* prefix, int ncells, int kmax_max,
-                           int sx, int nblocks, hipStream_t st) {
-  return launch_nt(k_pair_multi<T, N, OPT, NT, KM, MINW>, dim3(unsigned(nblocks)), NT,
-                   fwd_lds_bytes<T>(N, 2 * kmax_max + 1, sx), st, cells, prefix, ncells, sx);
-}
-
-template <class T, int NT, int OPT>
-ltmp2_status pair_multi_km(int kfix, const PairCell* cells, const long* prefix, int ncells,
-                           int kmax_max, int sx, int nblocks, hipStream_t st) {
-  constexpr int kw = kwin(N);
-  if (kfix >= 0 && kfix != kmax_max) return LTMP2_EINVAL;
-  if (kfix == kw) return pair_multi_go<T, NT, OPT, kw>(cells, prefix, ncells, kmax_max, sx, nblocks, st);
-  if constexpr (kw > 1)
-    if (kfix == kw - 1)
-      return pair_multi_go<T, NT, OPT, kw - 1>(cells, prefix, ncells, kmax_max, sx, nblocks, st);
-  if (kfix >= 0) return LTMP2_EINVAL;
-  return pair_multi_go<T, NT, OPT, -1>(cells, prefix, ncells, kmax_max, sx, nblocks, st);
+void pair_shape(int kmax, int ncol, int* planes, int* wg_per_cu) {
+  *planes = *wg_per_cu = 1;
+  (void)with_instance(kmax, [&](auto km) -> ltmp2_status {
+    constexpr int KM = decltype(km)::value, NT = pair_threads(sizeof(T), N, KM);
+    *planes = std::max(1, NT / N);
+    int n = 0;
+    const void* k = reinterpret_cast<const void*>(k_pair_multi<T, N, KM>);
+    if (ensure_lds(k, pair_lds<T, KM>(ncol)) &&
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, NT, pair_lds<T, KM>(ncol)) ==
+            hipSuccess)
+      *wg_per_cu = std::max(1, n);
+    return LTMP2_OK;
+  });
 }
 
 template <class T>
-struct PairMultiF {
-  template <int OPT>
-  struct F {
-    static ltmp2_status go(int kfix, const PairCell* cells, const long* prefix, int ncells,
-                           int kmax_max, int sx, int nblocks, hipStream_t st) {
-      if (sx < 1 || N % sx != 0 || sx > 10) return LTMP2_EINVAL;
-      if constexpr (sizeof(T) == sizeof(float) && OPT > 9) {
-        return LTMP2_EINVAL;
-      } else {
-        return pair_multi_km<T, kThreads, OPT>(kfix, cells, prefix, ncells, kmax_max, sx, nblocks,
-                                               st);
-      }
-    }
-  };
-};
-// Several cells of one grid size in one persistent launch; kfix is the kept
-// set all of them share (kwin(N) or kwin(N) - 1, see pair_kfix) or -1.
-template <class T>
-ltmp2_status pair_multi(const PairCell* cells, const long* prefix, int ncells, int ng_max,
-                        int kmax_max, int kfix, int sx, int nblocks, hipStream_t st) {
-  if constexpr (sizeof(T) == sizeof(float)) {
-    if (ng_max > 9 * kThreads) {
-      if (sx < 1 || N % sx != 0 || sx > 12) return LTMP2_EINVAL;
-      // the single-cell wide form: 256 threads, up to 17 outputs, two
-      // workgroups per CU when the slab fits half the shared memory
-      if constexpr (kwin(N) >= 9) {
-        constexpr int kw = kwin(N);
-        if (ng_max <= 17 * kThreads && fwd_lds_bytes<T>(N, 2 * kmax_max + 1, sx) <= kLdsHalf) {
-          if (kfix == kw)
-            return pair_multi_go<T, kThreads, 17, kw, 2>(cells, prefix, ncells, kmax_max, sx,
-                                                         nblocks, st);
-          if (kfix == kw - 1)
-            return pair_multi_go<T, kThreads, 17, kw - 1, 2>(cells, prefix, ncells, kmax_max,
-                                                             sx, nblocks, st);
-        }
-      }
-      if (ng_max > kWideOpt * kWideNT) return LTMP2_EINVAL;
-      return pair_multi_km<T, kWideNT, kWideOpt>(kfix, cells, prefix, ncells, kmax_max, sx,
-                                                  nblocks, st);
-    }
-    // a slab group of 129..192 z lines: 192-thread workgroups, one line each
-    if (sx >= 1 && sx <= 10 && N % sx == 0 && sx * N > 128 && sx * N <= kNarrowNT &&
-        ng_max <= 9 * kNarrowNT) {
-      if (ng_max <= 3 * kNarrowNT)
-        return pair_multi_km<T, kNarrowNT, 3>(kfix, cells, prefix, ncells, kmax_max, sx, nblocks,
-                                              st);
-      return pair_multi_km<T, kNarrowNT, 9>(kfix, cells, prefix, ncells, kmax_max, sx, nblocks,
-                                            st);
-    }
-  }
-  return by_opt<PairMultiF<T>::template F>(ng_max, kfix, cells, prefix, ncells, kmax_max, sx,
-                                           nblocks, st);
-}
-
-// Kept-set instance (kwin(N), kwin(N) - 1 or -1) the pair kernels use for kmax.
-int pair_kept_instance(int kmax) { return pair_kfix(kmax); }
-
-// Largest slab group of the pair transform that fits the shared memory.
-template <class T>
-int pair_sx_max(int kmax) {
-  return choose_sx_fwd<T>(2 * kmax + 1);
+ltmp2_status plane_order(const T* in, long ld, int nocc, T* out, hipStream_t st) {
+  return launch(k_plane_order<T>, dim3((N * N * N + 255) / 256, nocc), 0, st, in, ld, N, out);
 }
 
 // Explicit instantiation in both compilation passes, so the device pass
@@ -393,13 +279,12 @@ int pair_sx_max(int kmax) {
                                     int, double, double*, cplx<double>*, ShellBins,            \
                                     hipStream_t);                                              \
   template ltmp2_status wstates<T>(const T*, int, const int*, const signed char*, SphereCols,   \
-                                   int, double, cplx<T>*, long, hipStream_t);                  \
-  template ltmp2_status pair<T>(const T*, long, const cplx<T>*, int, const int*, int, int,     \
-                                const int*, int, const double*, int, double, double*,          \
-                                const signed char*, double*, int, int, hipStream_t);           \
-  template ltmp2_status pair_multi<T>(const PairCell*, const long*, int, int, int, int, int,   \
-                                      int, hipStream_t);                                       \
-  template int pair_sx_max<T>(int);                                                            \
+                                   int, double, T*, long, hipStream_t);                        \
+  template ltmp2_status pair<T>(const PairCell&, hipStream_t);                                 \
+  template ltmp2_status pair_multi<T>(const PairCell*, const long*, int, long, int, int,       \
+                                      hipStream_t);                                            \
+  template void pair_shape<T>(int, int, int*, int*);                                           \
+  template ltmp2_status plane_order<T>(const T*, long, int, T*, hipStream_t);                  \
   template ltmp2_status hartree<T>(const cplx<T>*, long, const int*, int, const double*, int,   \
                                    double, int, int, double*, hipStream_t);
 LTMP2_INST(double)
@@ -414,10 +299,12 @@ extern const GridOps<double> LTMP2_CAT(kGridOpsD_, LTMP2_N);
 extern const GridOps<float> LTMP2_CAT(kGridOpsF_, LTMP2_N);
 const GridOps<double> LTMP2_CAT(kGridOpsD_, LTMP2_N) = {
     orbitals<double>, overlap<double>, chi_rows<double>, chi_cols<double>, wstates<double>,
-    pair<double>, pair_multi<double>, hartree<double>, pair_sx_max<double>, pair_kept_instance};
+    pair<double>, pair_multi<double>, hartree<double>, pair_shape<double>, plane_order<double>,
+    pair_instance};
 const GridOps<float> LTMP2_CAT(kGridOpsF_, LTMP2_N) = {
     orbitals<float>, overlap<float>, chi_rows<float>, chi_cols<float>, wstates<float>,
-    pair<float>, pair_multi<float>, hartree<float>, pair_sx_max<float>, pair_kept_instance};
+    pair<float>, pair_multi<float>, hartree<float>, pair_shape<float>, plane_order<float>,
+    pair_instance};
 #endif
 
 }  // namespace ltmp2

@@ -1,0 +1,386 @@
+// Fock-like contraction (step (iv.b)) on real lines.
+//
+// For one outer G' and one occupied pair i <= j, with real orbitals psi and
+// complex transformed states w (their real and imaginary parts stored as
+// separate real fields):
+//   A_ij(G) = dV sum_r psi_i(r) w_j(r) e^{-iG.r},  G in the auxiliary set,
+//   xpart = sum_G v(G) [A_ij conj(A_ji) + A_ji conj(A_ij)]   (i < j)
+//         = sum_G v(G) |A_ii|^2                               (i = j).
+// Summed over pairs this is S_x(G') = sum_G v(G) sum_ij A_ij(G) A^{(-G')}_ji(-G),
+// using A^{(-G')}_ji(-G) = conj A^{(G')}_ji(G) for real orbitals.
+//
+// The auxiliary set contains -G with G and v depends on |G| only, so in the
+// sum over G the products of a real-part field with an imaginary-part field
+// cancel between G and -G: the two parts of w contribute separately, each
+// through the real fields f = psi_i u_j and g = psi_j u_i.  For real fields
+// the sum over the signs of (kx, ky, kz) turns into a sum over products of
+// cosines and sines per axis,
+//   sum_{signs} Re f^(G) conj g^(G) = m(kx) m(ky) m(kz) sum_{rows} F G,
+// m(0) = 1, m(k) = 2, where F is the real trigonometric transform of f: every
+// axis is a real transform of real lines (RFft) whose real and imaginary
+// parts become separate real rows, and no spectrum is ever unfolded.  Half
+// the registers of complex lines of the same length, and half the transform
+// work per part.
+//
+// What bounds it (counters and timing variants on the 27 and 36 grids): the
+// vector ALUs, the L1 reads (8 bytes per point and field at 64 B per clock)
+// and shared memory cost about the same, and only independent workgroups
+// overlap them, so the work is cut into small workgroups, as many per CU as
+// shared memory holds, with as few barriers per field as possible.  Complex
+// lines in 256-thread workgroups against this form, ns per item (one G', one
+// pair) in FP32: 12 grid 4.5 -> 2.4, 15: 10.2 -> 4.8, 18: 13.2 -> 8.7, 20:
+// 21.9 -> 11.3, 24: 31.0 -> 19.6, 27: 51.4 -> 35.7, 30: 88.5 -> 49, 36:
+// 112 -> 94; in FP64, 15: 19.4 -> 13.4, 20: 56 -> 38, 24: 77 -> 68, 27:
+// 189 -> 112.
+#pragma once
+#include "rfft.hpp"
+#include "transforms.hpp"
+
+namespace ltmp2 {
+
+// Everything one cell contributes to a pair launch.  Grid fields of the pair
+// transforms are stored z plane by z plane, r = (z N + x) N + y, so that the
+// z lines of consecutive (x, y) are consecutive in memory at every z: a wave
+// reads 256 contiguous bytes per z instead of pieces of several rows.
+struct PairCell {
+  const void* psi;     // [nocc][ld] orbitals (T)
+  const void* w;       // [gb][nocc][2][ld] real and imaginary parts of w (T)
+  const int* pairs;    // [npairs] i | j << 16
+  const int* cols;     // [ncol] kept (ky, kz) columns: row index ry | rz << 8
+  const double* vm2;   // [nm2] v(G) by m^2 = (|G| / b)^2, 0 outside the set
+  double* xpart;       // [gb][npairs] partial sums of this block
+  long ld;
+  int nocc, npairs, gb, kmax, ncol, nm2;
+  double dV2;
+  // optional split by auxiliary cutoff shell (ShellBins): number of spheres
+  // by m^2 (1 outside the set, where v = 0), the shells of the outer vectors
+  // from the block's first one on, and xbins [gb][npairs][nb]
+  const signed char* shm2 = nullptr;   // nullptr: no split
+  const signed char* shell = nullptr;  // shell of G' = shell[g0 + gl]
+  double* xbins = nullptr;
+  int nb = 0, g0 = 0;
+};
+
+// Rows of an axis: row 0 is k = 0, rows 2k - 1 and 2k are the cosine and sine
+// (real and imaginary) parts of k.
+__host__ __device__ constexpr int row_k(int r) { return (r + 1) / 2; }
+
+// Largest kept index of any auxiliary set the library takes (its vectors fit
+// the register outputs of the chi transforms: |m|^2 <= 101).
+constexpr int kAuxMax = 10, kAuxM2 = 101;
+
+// Kept-set instances compiled for a grid: the alias-free window kwin(N), one
+// below it, and everything the grid can hold.  A smaller kept set runs the
+// smallest instance that holds it (its extra rows are not among the columns).
+__host__ __device__ constexpr int pair_kw(int n) { return kwin(n) < kAuxMax ? kwin(n) : kAuxMax; }
+__host__ __device__ constexpr int pair_kf(int n) {
+  return (n - 1) / 2 < kAuxMax ? (n - 1) / 2 : kAuxMax;
+}
+
+// Most (ky, kz) columns a kept set with largest index k can have.
+__host__ __device__ constexpr int pair_cols_max(int k) {
+  int lim = (k + 1) * (k + 1) - 1, c = 0;
+  if (lim > kAuxM2) lim = kAuxM2;
+  for (int a = 0; a <= 2 * k; ++a)
+    for (int b = 0; b <= 2 * k; ++b)
+      c += row_k(a) * row_k(a) + row_k(b) * row_k(b) <= lim ? 1 : 0;
+  return c;
+}
+
+// Row stride of the line buffer: odd, against bank conflicts.
+__host__ __device__ constexpr int line_row(int n) { return n | 1; }
+
+// Shared memory: z-transformed lines of one slab of n / ns planes, and the
+// (ky, kz) columns of the planes of the earlier slabs.
+__host__ __device__ constexpr size_t pair_lds_bytes(size_t es, int n, int k, int ns, int ncol) {
+  return es * (size_t(n / ns) * (2 * k + 1) * line_row(n) + size_t(n - n / ns) * ncol);
+}
+
+// Slabs per field: one where the whole field fits next to a second workgroup
+// (each slab costs two more barriers: 27 grid, FP32, three workgroups per CU
+// of one slab 35.7 ns per item, four of three slabs 37.4), else the fewest
+// that leave room for two workgroups, else the fewest that fit at all.
+__host__ __device__ constexpr int pair_slabs(size_t es, int n, int k) {
+  const size_t stat = 2304;  // tables and reduction scratch
+  for (size_t cap : {size_t(80) * 1024, size_t(150) * 1024})
+    for (int ns = 1; ns <= n; ++ns)
+      if (n % ns == 0 && pair_lds_bytes(es, n, k, ns, pair_cols_max(k)) + stat <= cap) return ns;
+  return n;
+}
+
+// Threads per workgroup: at least one per column; beyond that the smallest
+// workgroups that still fill the CU's wave slots from its shared memory
+// (128 against 192 threads on the 18 grid 8.8 and 8.7 ns per item, 192 against
+// 320 on the 24 grid 18.3 and 22.2, 256 against 384 on the 27 grid 36 and 45,
+// 512 against 384 on the 36 grid 94 and 109; the 12 grid would run 64 threads
+// 3 % faster when the card is full, and loses 20 % to latency when it is not).
+__host__ __device__ constexpr int pair_threads(size_t es, int n, int k) {
+  const int cols = (pair_cols_max(k) + 63) / 64 * 64;
+  int nt = n <= 18 ? 128 : n <= 24 ? 192 : n <= 27 ? 256 : 512;
+  if (es == 8 && n == 18) nt = 192;
+  return cols > nt ? cols : nt;
+}
+
+// Waves per SIMD the launch bounds ask for: the register need is about three
+// line lengths (six in FP64).
+__host__ __device__ constexpr int pair_minw(size_t es, int n) {
+  if (es == 8) return n <= 12 ? 6 : n <= 18 ? 4 : n <= 24 ? 3 : 2;
+  return n <= 15 ? 8 : n <= 20 ? 6 : n <= 24 ? 5 : 4;
+}
+
+// Barrier that orders shared memory only: global loads stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Grid fields through buffer resources: the base in scalar registers, a
+// 32-bit lane offset, no 64-bit address arithmetic.  The field's address is
+// the same for every lane; taking it from the first lane tells the compiler
+// so.  Word 3 holds the gfx9-family default format; num_records bounds every
+// access to the field (reads past it return zero).
+template <class V>
+__device__ inline __amdgpu_buffer_rsrc_t field_rsrc(const V* p, unsigned n) {
+  const unsigned long long u = reinterpret_cast<unsigned long long>(p);
+  const unsigned lo = __builtin_amdgcn_readfirstlane(unsigned(u));
+  const unsigned hi = __builtin_amdgcn_readfirstlane(unsigned(u >> 32));
+  void* q = reinterpret_cast<void*>((static_cast<unsigned long long>(hi) << 32) | lo);
+  return __builtin_amdgcn_make_buffer_rsrc(q, short(0), int(n * sizeof(V)), 0x00020000);
+}
+template <class V>
+__device__ inline V field_load(__amdgpu_buffer_rsrc_t rs, unsigned off);
+template <>
+__device__ inline float field_load<float>(__amdgpu_buffer_rsrc_t rs, unsigned off) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+}
+template <>
+__device__ inline double field_load<double>(__amdgpu_buffer_rsrc_t rs, unsigned off) {
+  return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
+}
+
+// Trigonometric transform of the real field pa pu onto the columns: out[rx]
+// of column threadIdx.x.  Slab by slab, z lines (x, y) into the line buffer
+// t1 [SP][nk][R], y lines (x, rz) in place or, in all slabs but the last,
+// into the column buffer t2 [x][ncol]; then x lines per column.  Ends without
+// a barrier: t1 and t2 may be refilled after the caller's next one.
+template <class T, int N, int KM, int NT, int NS>
+__device__ __forceinline__ void line_transform(const T* pa, const T* pu, const PairCell& pc, T* t1,
+                                               T* t2, const int* rows, T (&out)[2 * KM + 1]) {
+  constexpr int R = line_row(N), nk = 2 * KM + 1, SP = N / NS, P = N * N;
+  const int tid = threadIdx.x;
+  const auto ra = field_rsrc(pa, P * N), ru = field_rsrc(pu, P * N);
+#pragma unroll 1
+  for (int s = 0; s < NS; ++s) {
+#pragma unroll 1
+    for (int l = tid; l < SP * N; l += NT) {
+      const unsigned r0 = unsigned(s * SP * N + l) * unsigned(sizeof(T));
+      T v[N], a[N], u[N];
+      cplx<T> X[N / 2 + 1];
+#pragma unroll
+      for (int z = 0; z < N; ++z) a[z] = field_load<T>(ra, r0 + unsigned(z * P * sizeof(T)));
+#pragma unroll
+      for (int z = 0; z < N; ++z) u[z] = field_load<T>(ru, r0 + unsigned(z * P * sizeof(T)));
+      // all loads of the line are issued before the first product waits (left
+      // to itself the compiler spaces them out: 24 grid 37 instead of 25 ns)
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int z = 0; z < N; ++z) v[z] = a[z] * u[z];
+      RFft<T, N>::run(v, X);
+      const int xs = l / N;
+      T* o = t1 + xs * (nk * R) + (l - xs * N);
+      o[0] = X[0].x;
+#pragma unroll
+      for (int k = 1; k <= KM; ++k) {
+        o[(2 * k - 1) * R] = X[k].x;
+        o[(2 * k) * R] = X[k].y;
+      }
+    }
+    lds_barrier();
+#pragma unroll 1
+    for (int l = tid; l < SP * nk; l += NT) {
+      T* row = t1 + l * R;
+      T v[N];
+      cplx<T> X[N / 2 + 1];
+#pragma unroll
+      for (int y = 0; y < N; ++y) v[y] = row[y];
+      RFft<T, N>::run(v, X);
+      if (NS > 1 && s + 1 < NS) {
+        const int xs = l / nk, m = rows[l - xs * nk], cnt = m >> 16;
+        T* d = t2 + (s * SP + xs) * pc.ncol + (m & 0xffff);
+        if (cnt > 0) d[0] = X[0].x;
+#pragma unroll
+        for (int k = 1; k <= KM; ++k)
+          if (2 * k < cnt) {
+            d[2 * k - 1] = X[k].x;
+            d[2 * k] = X[k].y;
+          }
+      } else {
+        row[0] = X[0].x;
+#pragma unroll
+        for (int k = 1; k <= KM; ++k) {
+          row[2 * k - 1] = X[k].x;
+          row[2 * k] = X[k].y;
+        }
+      }
+    }
+    lds_barrier();
+  }
+  if (tid < pc.ncol) {
+    const int cd = pc.cols[tid];
+    const T* c1 = t1 + (cd >> 8) * R + (cd & 0xff);
+    T v[N];
+    cplx<T> X[N / 2 + 1];
+#pragma unroll
+    for (int x = 0; x < N; ++x)
+      v[x] = (x < N - SP) ? t2[x * pc.ncol + tid] : c1[(x - (N - SP)) * (nk * R)];
+    RFft<T, N>::run(v, X);
+    out[0] = X[0].x;
+#pragma unroll
+    for (int k = 1; k <= KM; ++k) {
+      out[2 * k - 1] = X[k].x;
+      out[2 * k] = X[k].y;
+    }
+  }
+}
+
+// One (G', pair) item.  BINS: the per-shell split of the cutoff extrapolation
+// is compiled in (taken when pc.shm2 is set).
+template <class T, int N, int KM, bool BINS>
+__device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* t1) {
+  constexpr int NT = pair_threads(sizeof(T), N, KM), NS = pair_slabs(sizeof(T), N, KM);
+  constexpr int nk = 2 * KM + 1, SP = N / NS;
+  constexpr int kM2 = 2 * KM * KM + 2 * KM + 1;  // m^2 of any row triple lies below
+  __shared__ double vm[kM2];
+  __shared__ signed char sh[BINS ? kM2 : 1];
+  __shared__ int rows[NS > 1 ? nk : 1];
+  __shared__ double red[NT / 64 * (BINS ? kMaxShells : 1)];
+  const int tid = threadIdx.x;
+  const int i = pc.pairs[p] & 0xffff, j = pc.pairs[p] >> 16;
+  const T* psi = static_cast<const T*>(pc.psi);
+  const T* w = static_cast<const T*>(pc.w);
+  T* t2 = t1 + SP * nk * line_row(N);
+  const bool split = BINS && pc.shm2;
+  // tables by m^2 in shared memory: read one column at a time in the
+  // epilogue, a chain of dependent global reads otherwise (36 grid 115 -> 94)
+  for (int k = tid; k < pc.nm2; k += NT) {
+    vm[k] = pc.vm2[k];
+    if constexpr (BINS)
+      if (split) sh[k] = pc.shm2[k];
+  }
+  if constexpr (NS > 1) {
+    // first column and number of columns of each row rz (columns come in
+    // ascending (rz, ry) order)
+    for (int r = tid; r < nk; r += NT) rows[r] = 0;
+    __syncthreads();
+    for (int c = tid; c < pc.ncol; c += NT) {
+      const int rz = pc.cols[c] >> 8;
+      if (c + 1 == pc.ncol || (pc.cols[c + 1] >> 8) != rz) {
+        const int cnt = (pc.cols[c] & 0xff) + 1;
+        rows[rz] = (c + 1 - cnt) | (cnt << 16);
+      }
+    }
+    __syncthreads();
+  }
+  double s = 0.0;
+  double sb[kMaxShells] = {};
+  const int sg = split ? pc.shell[pc.g0 + gl] : 0;
+#pragma unroll 1
+  for (int part = 0; part < 2; ++part) {  // real, imaginary part of w
+    const T* ui = w + ((long(gl) * pc.nocc + i) * 2 + part) * pc.ld;
+    const T* uj = w + ((long(gl) * pc.nocc + j) * 2 + part) * pc.ld;
+    T xf[nk] = {}, xg[nk] = {};
+    line_transform<T, N, KM, NT, NS>(psi + long(i) * pc.ld, uj, pc, t1, t2, rows, xf);
+    lds_barrier();
+    if (i != j) {
+      line_transform<T, N, KM, NT, NS>(psi + long(j) * pc.ld, ui, pc, t1, t2, rows, xg);
+      lds_barrier();
+    } else {
+#pragma unroll
+      for (int k = 0; k < nk; ++k) xg[k] = xf[k];
+    }
+    if (tid < pc.ncol) {
+      const int cd = pc.cols[tid];
+      const int ky = row_k(cd & 0xff), kz = row_k(cd >> 8), r2 = ky * ky + kz * kz;
+      const double m = double((ky ? 2 : 1) * (kz ? 2 : 1));
+      const double* vt = vm + r2;
+      const double q0 = vt[0] * (double(xf[0]) * double(xg[0]));
+      if constexpr (BINS)
+        if (split) bin_add(sb, min(int(sh[r2]), sg) - 1, m * q0);
+      double q = 0.0;
+#pragma unroll
+      for (int k = 1; k <= KM; ++k) {
+        const double t = vt[k * k] * (double(xf[2 * k - 1]) * double(xg[2 * k - 1]) +
+                                      double(xf[2 * k]) * double(xg[2 * k]));
+        q += t;
+        if constexpr (BINS)
+          if (split) bin_add(sb, min(int(sh[r2 + k * k]), sg) - 1, 2.0 * m * t);
+      }
+      s += m * (q0 + 2.0 * q);
+    }
+  }
+  const double scale = (i == j ? 1.0 : 2.0) * pc.dV2;
+  s = block_sum(s, red);
+  if (tid == 0) pc.xpart[long(gl) * pc.npairs + p] = scale * s;
+  if constexpr (BINS) {
+    if (split) {
+      block_sum_bins(sb, red);
+      if (tid == 0)
+        for (int b = 0; b < pc.nb; ++b)
+          pc.xbins[(long(gl) * pc.npairs + p) * pc.nb + b] = scale * sb[b];
+    }
+  }
+}
+
+// One cell: workgroups are dispatched round-robin over the 8 XCDs; each XCD
+// gets a contiguous range of the (G', pair) list, whose pairs come in blocks
+// of (i, j), so the workgroups resident on one XCD share a handful of psi_i
+// and w_j^{(G')} in that XCD's L2.
+template <class T, int N, int KM, bool BINS>
+__global__ __launch_bounds__(pair_threads(sizeof(T), N, KM), pair_minw(sizeof(T), N)) void k_pair(
+    PairCell pc) {
+  extern __shared__ __align__(16) char smem[];
+  const long total = long(pc.npairs) * pc.gb;
+  const long per_xcd = (total + 7) / 8;
+  const long t = long(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (t >= total) return;
+  const int gl = int(t / pc.npairs);
+  pair_item<T, N, KM, BINS>(pc, gl, int(t - long(gl) * pc.npairs), reinterpret_cast<T*>(smem));
+}
+
+// Several cells of the same grid and kept-set instance in one launch: the
+// work list is the concatenation of every cell's (G', pair) items (prefix[c] =
+// first item of cell c), one item per workgroup, in XCD-contiguous ranges.
+template <class T, int N, int KM>
+__global__ __launch_bounds__(pair_threads(sizeof(T), N, KM),
+                             pair_minw(sizeof(T), N)) void k_pair_multi(const PairCell* __restrict__ cells,
+                                                                        const long* __restrict__ prefix,
+                                                                        int ncells) {
+  extern __shared__ __align__(16) char smem[];
+  const long total = prefix[ncells];
+  const long per_xcd = (total + 7) / 8;
+  const long t = long(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (blockIdx.x / 8 >= per_xcd || t >= total) return;
+  int lo = 0, hi = ncells - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (prefix[mid] <= t) lo = mid; else hi = mid - 1;
+  }
+  const PairCell pc = cells[lo];
+  const long u = t - prefix[lo];
+  const int gl = int(u / pc.npairs);
+  pair_item<T, N, KM, false>(pc, gl, int(u - long(gl) * pc.npairs), reinterpret_cast<T*>(smem));
+}
+
+// Occupied orbitals into the plane order of the pair transforms:
+// out[(z N + x) N + y] = in[(x N + z) N + y].  Grid (ceil(n^3 / 256), nocc).
+template <class T>
+__global__ __launch_bounds__(256) void k_plane_order(const T* __restrict__ in, long ld, int n,
+                                                     T* __restrict__ out) {
+  const int r = blockIdx.x * 256 + threadIdx.x;
+  if (r >= n * n * n) return;
+  const int y = r % n, x = (r / n) % n, z = r / (n * n);
+  out[long(blockIdx.y) * ld + r] = in[long(blockIdx.y) * ld + (x * n + z) * n + y];
+}
+
+}  // namespace ltmp2

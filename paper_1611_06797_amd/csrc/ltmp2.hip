@@ -308,6 +308,10 @@ ltmp2_status prepare_cell(ltmp2_ctx* c, const cplx<double>* d_coef) {
   if ((s = ops->overlap(static_cast<const T*>(c->d_psi), c->nrp, c->no, c->nv, c->d_gdesc, c->nh,
                         c->kmax_aux, c->dV, static_cast<cplx<T>*>(c->d_nd), c->stream)))
     return fail(nullptr, s, "overlap-density launch failed");
+  // (the stream orders this after the orbital synthesis's reads of d_coef)
+  if ((s = ops->plane_order(static_cast<const T*>(c->d_psi), c->nrp, c->no,
+                            static_cast<T*>(c->d_psiz), c->stream)))
+    return fail(nullptr, s, "orbital reordering launch failed");
   return LTMP2_OK;
 }
 
@@ -389,12 +393,13 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
 
   // internal cutoff extrapolation: number of nested spheres containing each
   // auxiliary vector (the same inclusive integer test as the auxiliary set)
-  std::vector<signed char> shell;
+  std::vector<signed char> shell, shm2;
+  std::vector<int> lims;
   if (P.n_extrap > 0) {
     c->nb = P.n_extrap;
     c->alpha = P.extrap_alpha > 0.0 ? P.extrap_alpha : 1.05;
     c->eaux_n.resize(c->nb);
-    std::vector<int> lims(c->nb);
+    lims.resize(c->nb);
     for (int q = 0; q < c->nb; ++q) {
       c->eaux_n[q] = P.eaux / std::pow(c->alpha, q);
       lims[q] = int(std::floor(2.0 * c->eaux_n[q] / (b * b) + 1e-9));
@@ -406,6 +411,29 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
       int sh = 0;
       while (sh < c->nb && m2 <= lims[sh]) ++sh;
       shell[k] = static_cast<signed char>(sh);
+    }
+  }
+
+  // pair transforms: columns (ky, kz) of the auxiliary sphere by row indices,
+  // and v(G) and the number of nested spheres by m^2
+  const int km_pair = P.prec == LTMP2_FP64 ? grid_ops<double>(n)->pair_kept(km)
+                                           : grid_ops<float>(n)->pair_kept(km);
+  if (km_pair < 0) return fail(nullptr, LTMP2_EINVAL, "auxiliary set too large");
+  std::vector<int> cols;
+  for (int rz = 0; rz <= 2 * km; ++rz)
+    for (int ry = 0; ry <= 2 * km; ++ry)
+      if (row_k(ry) * row_k(ry) + row_k(rz) * row_k(rz) <= lim) cols.push_back(ry | (rz << 8));
+  c->ncol = (int)cols.size();
+  c->nm2 = 2 * km_pair * km_pair + 2 * km_pair + 1;
+  std::vector<double> vm2(c->nm2, 0.0);
+  for (int m2 = 1; m2 < c->nm2 && m2 <= lim; ++m2)
+    vm2[m2] = 4.0 * M_PI / (c->omega * b * b * double(m2));
+  if (c->nb) {
+    shm2.assign(c->nm2, 1);
+    for (int m2 = 1; m2 < c->nm2 && m2 <= lim; ++m2) {
+      int sh = 0;
+      while (sh < c->nb && m2 <= lims[sh]) ++sh;
+      shm2[m2] = static_cast<signed char>(sh);
     }
   }
 
@@ -489,11 +517,9 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
   }
   // pairs i <= j in blocks of (i, j): the workgroups resident on one XCD take
   // consecutive items and share the block's orbitals and transformed states
-  // in that XCD's L2 and the Infinity Cache.  8 x 8 blocks; 16 x 16 for the
-  // wide 512-thread pair form (auxiliary sets above 2304 vectors), measured
-  // 2 % faster there.
+  // in that XCD's L2 and the Infinity Cache.
   std::vector<int> pairs;
-  const int kPairBlock = (P.prec != LTMP2_FP64 && c->ng > 9 * kThreads) ? 16 : 8;
+  const int kPairBlock = 8;
   for (int bi = 0; bi < c->no; bi += kPairBlock)
     for (int bj = bi; bj < c->no; bj += kPairBlock)
       for (int i = bi; i < std::min(bi + kPairBlock, c->no); ++i)
@@ -577,7 +603,8 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
   if ((s = upload(c, &c->d_cdesc, cdesc)) || (s = upload(c, &c->d_cstart, cstart)) ||
       (s = upload(c, &c->d_ckx, ckx)) || (s = upload(c, &c->d_wq, wq)) ||
       (s = upload(c, &c->d_wsgn, wsgn)) || (s = upload(c, &c->d_gdesc, gdesc)) ||
-      (s = upload(c, &c->d_pairs, pairs)) || (s = upload(c, &c->d_v, v)) ||
+      (s = upload(c, &c->d_pairs, pairs)) || (s = upload(c, &c->d_cols, cols)) ||
+      (s = upload(c, &c->d_vm2, vm2)) || (s = upload(c, &c->d_v, v)) ||
       (s = upload(c, &c->d_fo, fo)) || (s = upload(c, &c->d_fv, fv)))
     return s;
   if (es == sizeof(double)) {
@@ -591,8 +618,14 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
     c->d_bpw = d;
   }
   c->sc = SphereCols{(int)cdesc.size(), ko, c->d_cdesc, c->d_cstart, c->d_ckx};
+  // the coefficients are needed until the orbitals are on the grid; their
+  // memory then holds the occupied orbitals in the pair transforms' order
+  const size_t psiz_bytes = es * size_t(c->no) * nrp;
   double* d_coef = nullptr;
-  if ((s = upload(c, &d_coef, coef_col))) return s;
+  if ((s = dalloc(c, &d_coef, std::max(coef_col.size(), psiz_bytes / sizeof(double) + 1)))) return s;
+  HIPCHK(c, hipMemcpy(d_coef, coef_col.data(), coef_col.size() * sizeof(double),
+                      hipMemcpyHostToDevice));
+  c->d_psiz = d_coef;
   if ((s = dalloc_bytes(c, &c->d_psi, es * size_t(c->nst) * nrp)) ||
       (s = dalloc_bytes(c, &c->d_nd, es * 2 * size_t(c->nv) * c->nh * c->no)) ||
       (c->own_scratch && (s = dalloc_bytes(c, &c->d_chi, es * nrp * nrp))) ||
@@ -615,7 +648,8 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
     HIPCHK(c, hipMemsetAsync(c->d_b3l, 0, bb, c->stream));
   }
   if (c->nb) {
-    if ((s = upload(c, &c->d_shell, shell)) || (s = dalloc(c, &c->d_pdb, size_t(c->nh) * c->nb)) ||
+    if ((s = upload(c, &c->d_shell, shell)) || (s = upload(c, &c->d_shm2, shm2)) ||
+        (s = dalloc(c, &c->d_pdb, size_t(c->nh) * c->nb)) ||
         (s = dalloc(c, &c->d_xb, size_t(c->nh) * c->npairs * c->nb)) ||
         (s = dalloc(c, &c->d_xrowb, size_t(c->nh) * c->nb)) ||
         (s = dalloc(c, &c->d_scalb, 2 * size_t(c->ntau) * c->nb)))
@@ -758,7 +792,7 @@ ltmp2_status block_prepare_t(ltmp2_ctx* c, int itau, int g0, int gb) {
   {
     StageTimer tm(c, 4);
     s = ops->wstates(static_cast<const T*>(c->d_P), c->npw, c->d_wq, c->d_wsgn, c->sc, gb * c->no,
-                     1.0 / std::sqrt(c->omega), static_cast<cplx<T>*>(c->d_w), c->nrp, c->stream);
+                     1.0 / std::sqrt(c->omega), static_cast<T*>(c->d_w), c->nrp, c->stream);
   }
   if (s) return fail(c, s, "transformed-state launch failed");
   return LTMP2_OK;
@@ -768,12 +802,15 @@ template <class T>
 ltmp2_status block_pair_t(ltmp2_ctx* c, int g0, int gb) {
   const GridOps<T>* ops = grid_ops<T>(c->n);
   StageTimer tm(c, 5);
-  ltmp2_status s = ops->pair(static_cast<const T*>(c->d_psi), c->nrp,
-                             static_cast<const cplx<T>*>(c->d_w), c->no, c->d_pairs, c->npairs, gb,
-                             c->d_gdesc, c->ng, c->d_v, c->kmax_aux, c->dV * c->dV,
-                             c->d_xpart + size_t(g0) * c->npairs, c->d_shell,
-                             c->nb ? c->d_xb + size_t(g0) * c->npairs * c->nb : nullptr, c->nb,
-                             g0, c->stream);
+  PairCell pc = pair_cell(c, g0, gb);
+  if (c->nb) {
+    pc.shm2 = c->d_shm2;
+    pc.shell = c->d_shell;
+    pc.xbins = c->d_xb + size_t(g0) * c->npairs * c->nb;
+    pc.nb = c->nb;
+    pc.g0 = g0;
+  }
+  ltmp2_status s = ops->pair(pc, c->stream);
   if (s) return fail(c, s, "pair transform launch failed");
   return LTMP2_OK;
 }
@@ -888,8 +925,8 @@ ltmp2_status hartree_tau_t(ltmp2_ctx* c, int itau) {
   for (int g0 = 0; g0 < c->nh; g0 += c->gblock) {
     const int gb = std::min(c->gblock, c->nh - g0);
     if ((s = block_prepare(c, itau, g0, gb))) return s;
-    if ((s = launch_hsum<T>(static_cast<const T*>(c->d_psi), c->nrp,
-                            static_cast<const cplx<T>*>(c->d_w), c->no, c->nr, gb, h, c->stream)))
+    if ((s = launch_hsum<T>(static_cast<const T*>(c->d_psiz), c->nrp,
+                            static_cast<const T*>(c->d_w), c->no, c->nr, gb, h, c->stream)))
       return fail(c, s, "state-sum launch failed");
     if ((s = ops->hartree(h, c->nrp, c->d_gdesc, c->ng, c->d_v, c->kmax_aux, c->dV, g0, gb,
                           c->d_pd, c->stream)))
@@ -921,6 +958,11 @@ extern "C" ltmp2_status ltmp2_direct_hartree(ltmp2_ctx* c, int itau, double* e_d
 }
 
 namespace ltmp2 {
+PairCell pair_cell(const ltmp2_ctx* c, int g0, int gb) {
+  return PairCell{c->d_psiz, c->d_w,  c->d_pairs, c->d_cols,   c->d_vm2,
+                  c->d_xpart + size_t(g0) * c->npairs, c->nrp, c->no, c->npairs, gb,
+                  c->kmax_aux, c->ncol, c->nm2, c->dV * c->dV};
+}
 ltmp2_status run_direct(ltmp2_ctx* c, int itau, double* chi_out) {
   return direct_tau(c, itau, chi_out);
 }

@@ -134,16 +134,16 @@ template ltmp2_status launch_gemm_kmajor<kBF16x3>(const void*, long, const void*
                                                   const double*, int, int, hipStream_t);
 
 template <class T>
-ltmp2_status launch_hsum(const T* psi, long ld, const cplx<T>* w, int no, long nr, int gb,
+ltmp2_status launch_hsum(const T* psi, long ld, const T* w, int no, long nr, int gb,
                          cplx<T>* h, hipStream_t st) {
   if (gb <= 0) return LTMP2_OK;
   hipLaunchKernelGGL(k_hsum<T>, dim3(unsigned((nr + 255) / 256), unsigned(gb)), dim3(256), 0, st,
                      psi, ld, w, no, nr, h);
   return hipGetLastError() == hipSuccess ? LTMP2_OK : LTMP2_EDEVICE;
 }
-template ltmp2_status launch_hsum<double>(const double*, long, const cplx<double>*, int, long,
+template ltmp2_status launch_hsum<double>(const double*, long, const double*, int, long,
                                           int, cplx<double>*, hipStream_t);
-template ltmp2_status launch_hsum<float>(const float*, long, const cplx<float>*, int, long, int,
+template ltmp2_status launch_hsum<float>(const float*, long, const float*, int, long, int,
                                          cplx<float>*, hipStream_t);
 
 __global__ void k_widen(const float* in, double* out, long n) {

@@ -239,121 +239,6 @@ __device__ __forceinline__ void forward_pruned(const Load& ld, int nf_active, in
   }
 }
 
-// Both fields of forward_pruned (NF = 2) side by side: two slab buffers
-// (fwd2_lds), so every pass works on the lines, rows and columns of both
-// fields at once.  For a slab of sx planes the z pass has 2 sx N lines, the
-// y pass 2 sx nk rows and the x stage 2 nk^2 columns, which fill a wide
-// workgroup better than one field at a time, with half the barriers.  Same
-// arithmetic, same order per field, as forward_pruned.
-template <class T>
-__host__ __device__ inline size_t fwd2_lds_bytes(int n, int nk, int sx) {
-  return sizeof(cplx<T>) * (2 * size_t(sx) * nk * slab_row(n) + n);
-}
-
-template <class T>
-__device__ inline SlabLds<T> fwd2_lds(void* base, int n, int nk, int sx) {
-  SlabLds<T> s;
-  s.t1 = reinterpret_cast<cplx<T>*>(base);
-  s.tw = s.t1 + 2 * size_t(sx) * nk * slab_row(n);
-  s.cmap = nullptr;
-  return s;
-}
-
-template <class T, int S, int D, int NT>
-__device__ inline void column_fft_rows2(cplx<T>* a, int nf, int nk, int R, int pstride,
-                                        int fstride) {
-  const int nc = nk * nk;
-  const unsigned inv = 0xffffffffu / unsigned(nk) + 1u;
-  for (int c = threadIdx.x; c < nf * nc; c += NT) {
-    const int f = c >= nc ? 1 : 0, cc = c - f * nc;
-    const int kzi = int(__umulhi(unsigned(cc), inv)), kyi = cc - kzi * nk;
-    cplx<T>* b = a + f * fstride + kzi * R + kyi;
-    cplx<T> v[D];
-#pragma unroll
-    for (int k = 0; k < D; ++k) v[k] = b[k * pstride];
-    Fft<T, S, D>::run(v);
-#pragma unroll
-    for (int k = 0; k < D; ++k) b[k * pstride] = v[k];
-  }
-}
-
-template <class T, int S, int N, int NT>
-__device__ inline void column_fft_rows2_tile(cplx<T>* a, int d, int nf, int nk, int R,
-                                             int pstride, int fstride) {
-  if constexpr (N % 12 == 0) if (d == 12) return column_fft_rows2<T, S, 12, NT>(a, nf, nk, R, pstride, fstride);
-  if constexpr (N % 10 == 0) if (d == 10) return column_fft_rows2<T, S, 10, NT>(a, nf, nk, R, pstride, fstride);
-  if constexpr (N % 9 == 0) if (d == 9) return column_fft_rows2<T, S, 9, NT>(a, nf, nk, R, pstride, fstride);
-  if constexpr (N % 8 == 0) if (d == 8) return column_fft_rows2<T, S, 8, NT>(a, nf, nk, R, pstride, fstride);
-  if constexpr (N % 6 == 0) if (d == 6) return column_fft_rows2<T, S, 6, NT>(a, nf, nk, R, pstride, fstride);
-  if constexpr (N % 5 == 0) if (d == 5) return column_fft_rows2<T, S, 5, NT>(a, nf, nk, R, pstride, fstride);
-  if constexpr (N % 4 == 0) if (d == 4) return column_fft_rows2<T, S, 4, NT>(a, nf, nk, R, pstride, fstride);
-  if constexpr (N % 3 == 0) if (d == 3) return column_fft_rows2<T, S, 3, NT>(a, nf, nk, R, pstride, fstride);
-  if constexpr (N % 2 == 0) if (d == 2) return column_fft_rows2<T, S, 2, NT>(a, nf, nk, R, pstride, fstride);
-}
-
-template <class T, int S, int N, int OPT, int NT = kThreads, int KM = -1, class Load>
-__device__ __forceinline__ void forward_pruned_joint(const Load& ld, int nf_active, int kmax_rt,
-                                                     int sx, const int (&gdesc)[OPT], int nout,
-                                                     cplx<T> (&acc)[2][OPT],
-                                                     const SlabLds<T>& L) {
-  constexpr int R = slab_row(N);
-  const int kmax = KM >= 0 ? KM : kmax_rt;
-  const int nk = 2 * kmax + 1, M = N / sx, pstride = nk * R, fstride = sx * pstride;
-  const int tid = threadIdx.x;
-  const int nl = sx * N, nr = sx * nk;
-  int ox[OPT];
-#pragma unroll
-  for (int t = 0; t < OPT; ++t) {
-    const int kxm = gdesc[t] & 0xff, kyi = (gdesc[t] >> 8) & 0xff, kzi = gdesc[t] >> 16;
-    ox[t] = ((kxm % sx) * pstride + kzi * R + kyi) | (kxm << 24);
-  }
-  for (int x2 = 0; x2 < M; ++x2) {
-    // z pass: line (f, xs, y) -> rows (f, xs, kz)
-    for (int l = tid; l < nf_active * nl; l += NT) {
-      const int f = l >= nl ? 1 : 0, lf = l - f * nl;
-      const int xs = lf / N, y = lf - xs * N, x = x2 + M * xs;
-      cplx<T> v[N];
-#pragma unroll
-      for (int z = 0; z < N; ++z) v[z] = ld(f, x, y, z);
-      Fft<T, S, N>::run(v);
-      cplx<T>* out = L.t1 + f * fstride + xs * pstride + y;
-#pragma unroll
-      for (int z = 0; z < N; ++z) {
-        const int kz = (z <= N / 2) ? z : z - N;
-        if (kz >= -kmax && kz <= kmax) out[(kz + kmax) * R] = v[z];
-      }
-    }
-    __syncthreads();
-    // y pass: row (f, xs, kz) in place; the kept ky land at the row's start
-    for (int l = tid; l < nf_active * nr; l += NT) {
-      const int f = l >= nr ? 1 : 0;
-      cplx<T>* row = L.t1 + f * fstride + (l - f * nr) * R;
-      cplx<T> v[N];
-#pragma unroll
-      for (int y = 0; y < N; ++y) v[y] = row[y];
-      Fft<T, S, N>::run(v);
-#pragma unroll
-      for (int y = 0; y < N; ++y) {
-        const int ky = (y <= N / 2) ? y : y - N;
-        if (ky >= -kmax && ky <= kmax) row[ky + kmax] = v[y];
-      }
-    }
-    __syncthreads();
-    column_fft_rows2_tile<T, S, N, NT>(L.t1, sx, nf_active, nk, R, pstride, fstride);
-    if (sx > 1) __syncthreads();
-#pragma unroll
-    for (int t = 0; t < OPT; ++t) {
-      const int o = tid + t * NT;
-      if (o < nout) {
-        const cplx<T> tw = L.tw[((ox[t] >> 24) * x2) % N];
-        acc[0][t] = cfma(tw, L.t1[ox[t] & 0xffffff], acc[0][t]);
-        if (nf_active > 1) acc[1][t] = cfma(tw, L.t1[fstride + (ox[t] & 0xffffff)], acc[1][t]);
-      }
-    }
-    __syncthreads();  // the next z pass overwrites the rows
-  }
-}
-
 // Inverse transform of NF coefficient vectors given on a sphere whose
 // entries are grouped in (ky, kz) columns: column c covers entries
 // [cstart[c], cstart[c+1]) with packed (ky + kmax) | (kz + kmax) << 8 in
