@@ -16,9 +16,11 @@
 #include <cmath>
 #include <cstdint>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <string>
 #include <thread>
+#include <utility>
 #include <vector>
 
 #include "../../include/ltmp2.h"
@@ -55,83 +57,193 @@ __global__ void k_lin_fwd(const float* __restrict__ X, int B, int I, const float
   Y[t] = act ? tanhf(s) : s;
 }
 
-// dX[b][i] = (sum_o dY[b][o] W[o][i]) * (1 - A[b][i]^2)   (A = tanh output feeding W)
-__global__ void k_lin_bwd_x(const float* __restrict__ dY, int B, int O, const float* __restrict__ W,
-                            int I, const float* __restrict__ A, float* __restrict__ dX) {
-  const long t = long(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= long(B) * I) return;
-  const int b = int(t / I), i = int(t - long(b) * I);
-  float s = 0.f;
-  for (int o = 0; o < O; ++o) s += dY[long(b) * O + o] * W[o * I + i];
-  const float a = A[t];
-  dX[t] = s * (1.f - a * a);
-}
+// Loss and gradient of one minibatch in two launches.
+//
+// k_mlp_step: workgroups walk the batch in chunks of kS samples.  The whole
+// network (24 KB) and a chunk's activations sit in shared memory; forward,
+// masked squared error, backward and the chunk's weight gradients follow one
+// another between barriers, and each thread keeps its share of the gradient
+// in registers over all its chunks.  part [workgroups][kP], lossb
+// [workgroups].  k_mlp_reduce adds the workgroups' parts in fixed order and,
+// when training, applies Adam, one thread per parameter.
+//
+// Bound by latency (0.2 GFLOP per 1024 samples): one kernel per layer and
+// direction, with the weight gradients summed over the batch by 17 workgroups
+// (234 us per launch), took 800 us a step of 1024 samples.
+constexpr int kS = 16, kStep = 256, kW = kH + 1;  // kW: padded row, any read order is conflict-free
+constexpr int kMaxParts = 256;
 
-// dW[o][i] = sum_b dY[b][o] X[b][i] (threads o*I + i), db[o] = sum_b dY[b][o]
-__global__ void k_lin_bwd_w(const float* __restrict__ dY, const float* __restrict__ X, int B,
-                            int O, int I, float* __restrict__ dW, float* __restrict__ db) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < O * I) {
-    const int o = t / I, i = t - o * I;
-    float s = 0.f;
-    for (int b = 0; b < B; ++b) s += dY[long(b) * O + o] * X[long(b) * I + i];
-    dW[t] = s;
-  } else if (t < O * I + O) {
-    const int o = t - O * I;
-    float s = 0.f;
-    for (int b = 0; b < B; ++b) s += dY[long(b) * O + o];
-    db[o] = s;
+__global__ __launch_bounds__(kStep) void k_mlp_step(const float* __restrict__ P,
+                                                    const float* __restrict__ X,
+                                                    const float* __restrict__ Y,
+                                                    const float* __restrict__ M,
+                                                    const int* __restrict__ idx, int B,
+                                                    float inv_count, float* __restrict__ part,
+                                                    float* __restrict__ lossb) {
+  __shared__ float W1[kH * kIn], b1[kH], W2[kH * kW], b2[kH], W3[kOut * kW], b3[kOut];
+  __shared__ float x[kS][kIn], h1[kS][kW], h2[kS][kW], d1[kS][kW], d2[kS][kW], dO[kS][kOut];
+  __shared__ float red[kStep];
+  const int t = threadIdx.x;
+  for (int k = t; k < kP; k += kStep) {
+    int q = k;
+    const float v = P[k];
+    if (q < kH * kIn) W1[q] = v;
+    else if ((q -= kH * kIn) < kH) b1[q] = v;
+    else if ((q -= kH) < kH * kH) W2[q / kH * kW + q % kH] = v;
+    else if ((q -= kH * kH) < kH) b2[q] = v;
+    else if ((q -= kH) < kOut * kH) W3[q / kH * kW + q % kH] = v;
+    else b3[q - kOut * kH] = v;
   }
-}
-
-// masked squared error: dOut = 2 (out - y) m / count, lossb[b] = sum_k m (out - y)^2
-__global__ void k_mse(const float* __restrict__ out, const float* __restrict__ y,
-                      const float* __restrict__ m, int B, int K, float inv_count,
-                      float* __restrict__ dout, float* __restrict__ lossb) {
-  const int b = blockIdx.x * blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  float s = 0.f;
-  for (int k = 0; k < K; ++k) {
-    const long q = long(b) * K + k;
-    const float d = (out[q] - y[q]) * m[q];
-    dout[q] = 2.f * d * inv_count;
-    s += d * d;
+  // gradient entries of this thread: W2[o2][i2 .. i2 + 15], six of W3, one of
+  // W1 and one bias
+  float g2[16] = {}, g3[6] = {}, g1 = 0.f, gb = 0.f, loss = 0.f;
+  const int o2 = t / 4, i2 = t % 4 * 16;
+  const int o = t & 63, bq = t >> 6;  // forward / backward: output o of samples bq, bq + 4, ...
+  for (int c0 = blockIdx.x * kS; c0 < B; c0 += gridDim.x * kS) {
+    const int nb = min(kS, B - c0);
+    __syncthreads();
+    if (t < kS * kIn) {
+      const int b = t / kIn;
+      x[b][t % kIn] = b < nb ? X[long(idx ? idx[c0 + b] : c0 + b) * kIn + t % kIn] : 0.f;
+    }
+    __syncthreads();
+    for (int b = bq; b < kS; b += 4) {
+      float s = b1[o];
+      for (int i = 0; i < kIn; ++i) s += x[b][i] * W1[o * kIn + i];
+      h1[b][o] = tanhf(s);
+    }
+    __syncthreads();
+    {
+      float s[kS / 4];
+#pragma unroll
+      for (int u = 0; u < kS / 4; ++u) s[u] = b2[o];
+#pragma unroll 8
+      for (int i = 0; i < kH; ++i) {
+        const float w = W2[o * kW + i];
+#pragma unroll
+        for (int u = 0; u < kS / 4; ++u) s[u] += h1[bq + 4 * u][i] * w;
+      }
+#pragma unroll
+      for (int u = 0; u < kS / 4; ++u) h2[bq + 4 * u][o] = tanhf(s[u]);
+    }
+    __syncthreads();
+    for (int e = t; e < kS * kOut; e += kStep) {
+      const int b = e / kOut, k = e - b * kOut;
+      float s = b3[k];
+#pragma unroll 8
+      for (int i = 0; i < kH; ++i) s += h2[b][i] * W3[k * kW + i];
+      float d = 0.f;
+      if (b < nb) {
+        const long r = long(idx ? idx[c0 + b] : c0 + b) * kOut + k;
+        d = (s - Y[r]) * M[r];
+      }
+      dO[b][k] = 2.f * d * inv_count;
+      loss += d * d;
+    }
+    __syncthreads();
+    {
+      float s[kS / 4] = {};
+#pragma unroll 8
+      for (int k = 0; k < kOut; ++k) {
+        const float w = W3[k * kW + o];
+#pragma unroll
+        for (int u = 0; u < kS / 4; ++u) s[u] += dO[bq + 4 * u][k] * w;
+      }
+#pragma unroll
+      for (int u = 0; u < kS / 4; ++u) {
+        const float a = h2[bq + 4 * u][o];
+        d2[bq + 4 * u][o] = s[u] * (1.f - a * a);
+      }
+    }
+    __syncthreads();
+    {
+      float s[kS / 4] = {};
+#pragma unroll 8
+      for (int k = 0; k < kH; ++k) {
+        const float w = W2[k * kW + o];
+#pragma unroll
+        for (int u = 0; u < kS / 4; ++u) s[u] += d2[bq + 4 * u][k] * w;
+      }
+#pragma unroll
+      for (int u = 0; u < kS / 4; ++u) {
+        const float a = h1[bq + 4 * u][o];
+        d1[bq + 4 * u][o] = s[u] * (1.f - a * a);
+      }
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int b = 0; b < kS; ++b) {
+      const float d = d2[b][o2];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) g2[u] += d * h1[b][i2 + u];
+#pragma unroll
+      for (int u = 0; u < 6; ++u) {
+        const int e = t + u * kStep;
+        g3[u] += dO[b][e >> 6] * h2[b][e & 63];
+      }
+    }
+    for (int b = 0; b < kS; ++b) {
+      if (t < kH * kIn) g1 += d1[b][t / kIn] * x[b][t % kIn];
+      if (t < kH) gb += d1[b][t];
+      else if (t < 2 * kH) gb += d2[b][t - kH];
+      else if (t < 2 * kH + kOut) gb += dO[b][t - 2 * kH];
+    }
   }
-  lossb[b] = s;
-}
-
-__global__ void k_sum(const float* __restrict__ x, int n, float* __restrict__ out) {
-  __shared__ float red[256];
-  float s = 0.f;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) s += x[i];
-  red[threadIdx.x] = s;
+  float* G = part + long(blockIdx.x) * kP;
+  if (t < kH * kIn) G[t] = g1;
+  G += kH * kIn;
+  if (t < kH) G[t] = gb;
+  G += kH;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) G[o2 * kH + i2 + u] = g2[u];
+  G += kH * kH;
+  if (t >= kH && t < 2 * kH) G[t - kH] = gb;
+  G += kH;
+#pragma unroll
+  for (int u = 0; u < 6; ++u) G[t + u * kStep] = g3[u];
+  G += kOut * kH;
+  if (t >= 2 * kH && t < 2 * kH + kOut) G[t - 2 * kH] = gb;
+  red[t] = loss;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
+  for (int w = kStep / 2; w > 0; w >>= 1) {
+    if (t < w) red[t] += red[t + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[0] += red[0];
+  if (t == 0) lossb[blockIdx.x] = red[0];
 }
 
-__global__ void k_adam(float* __restrict__ p, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, int n, float lr, float b1, float b2, float eps,
-                       float bc1, float bc2) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
+struct Adam {
+  float lr, b1, b2, eps, bc1, bc2;
+};
+
+// g[p] = sum_w part[w][p]; loss[0] += sum_w lossb[w]; with m: Adam step of p
+__global__ __launch_bounds__(256) void k_mlp_reduce(const float* __restrict__ part, int nw,
+                                                    const float* __restrict__ lossb,
+                                                    float* __restrict__ g, float* __restrict__ loss,
+                                                    float* __restrict__ p, float* __restrict__ m,
+                                                    float* __restrict__ v, Adam ad) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (blockIdx.x == 0) {
+    __shared__ float red[256];
+    red[threadIdx.x] = int(threadIdx.x) < nw ? lossb[threadIdx.x] : 0.f;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+      if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
+      __syncthreads();
+    }
+    if (threadIdx.x == 0) loss[0] += red[0];
+  }
+  if (i >= kP) return;
+  float gi = 0.f;
+#pragma unroll 16
+  for (int w = 0; w < nw; ++w) gi += part[long(w) * kP + i];
+  g[i] = gi;
+  if (!m) return;
+  const float mi = ad.b1 * m[i] + (1.f - ad.b1) * gi;
+  const float vi = ad.b2 * v[i] + (1.f - ad.b2) * gi * gi;
   m[i] = mi;
   v[i] = vi;
-  p[i] -= lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
-}
-
-__global__ void k_gather(const float* __restrict__ src, const int* __restrict__ idx, int B, int K,
-                         float* __restrict__ dst) {
-  const long t = long(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= long(B) * K) return;
-  const int b = int(t / K), k = int(t - long(b) * K);
-  dst[t] = src[long(idx[b]) * K + k];
+  p[i] -= ad.lr * (mi / ad.bc1) / (sqrtf(vi / ad.bc2) + ad.eps);
 }
 
 namespace {
@@ -147,62 +259,52 @@ inline uint64_t splitmix64(uint64_t& s) {
 }
 inline double uniform01(uint64_t& s) { return double(splitmix64(s) >> 11) * 0x1.0p-53; }
 
-// Device workspace of one forward/backward pass over a batch.
+// Device memory of one call, one allocation cut into 256-byte aligned pieces.
 struct Work {
-  float *P, *G, *X, *Y, *M, *H1, *H2, *O, *dO, *dH2, *dH1, *lossb, *loss;
-  std::vector<void*> owned;
+  char* base = nullptr;
+  size_t used = 0;
   ~Work() {
-    for (void* p : owned) (void)hipFree(p);
+    if (base) (void)hipFree(base);
   }
-  bool alloc(float** p, size_t n) {
+  static size_t piece(size_t n) { return (std::max<size_t>(n, 1) * sizeof(float) + 255) / 256 * 256; }
+  bool init(std::initializer_list<std::pair<float**, size_t>> want) {
+    size_t total = 0;
+    for (auto& w : want) total += piece(w.second);
     void* q = nullptr;
-    if (hipMalloc(&q, std::max<size_t>(n, 1) * sizeof(float)) != hipSuccess) return false;
-    owned.push_back(q);
-    *p = static_cast<float*>(q);
+    if (hipMalloc(&q, total) != hipSuccess) return false;
+    base = static_cast<char*>(q);
+    for (auto& w : want) {
+      *w.first = reinterpret_cast<float*>(base + used);
+      used += piece(w.second);
+    }
     return true;
-  }
-  bool init(int B) {
-    return alloc(&P, kP) && alloc(&G, kP) && alloc(&X, size_t(B) * kIn) &&
-           alloc(&Y, size_t(B) * kOut) && alloc(&M, size_t(B) * kOut) &&
-           alloc(&H1, size_t(B) * kH) && alloc(&H2, size_t(B) * kH) &&
-           alloc(&O, size_t(B) * kOut) && alloc(&dO, size_t(B) * kOut) &&
-           alloc(&dH2, size_t(B) * kH) && alloc(&dH1, size_t(B) * kH) && alloc(&lossb, B) &&
-           alloc(&loss, 1);
   }
 };
 
-void forward(const Work& w, int B, hipStream_t st) {
-  Net n = unpack(w.P);
-  hipLaunchKernelGGL(k_lin_fwd, dim3(nblk(long(B) * kH)), dim3(256), 0, st, w.X, B, kIn, n.W1,
-                     n.b1, kH, 1, w.H1);
-  hipLaunchKernelGGL(k_lin_fwd, dim3(nblk(long(B) * kH)), dim3(256), 0, st, w.H1, B, kH, n.W2,
-                     n.b2, kH, 1, w.H2);
-  hipLaunchKernelGGL(k_lin_fwd, dim3(nblk(long(B) * kOut)), dim3(256), 0, st, w.H2, B, kH, n.W3,
-                     n.b3, kOut, 0, w.O);
+void forward(const float* P, const float* X, int B, float* h1, float* h2, float* O,
+             hipStream_t st) {
+  Net n = unpack(P);
+  hipLaunchKernelGGL(k_lin_fwd, dim3(nblk(long(B) * kH)), dim3(256), 0, st, X, B, kIn, n.W1, n.b1,
+                     kH, 1, h1);
+  hipLaunchKernelGGL(k_lin_fwd, dim3(nblk(long(B) * kH)), dim3(256), 0, st, h1, B, kH, n.W2, n.b2,
+                     kH, 1, h2);
+  hipLaunchKernelGGL(k_lin_fwd, dim3(nblk(long(B) * kOut)), dim3(256), 0, st, h2, B, kH, n.W3,
+                     n.b3, kOut, 0, O);
 }
 
-// gradient of the masked MSE into w.G; loss (mean) accumulated into w.loss
-void backward(const Work& w, int B, float inv_count, hipStream_t st) {
-  Net n = unpack(w.P);
-  float* gW1 = w.G;
-  float* gb1 = gW1 + kH * kIn;
-  float* gW2 = gb1 + kH;
-  float* gb2 = gW2 + kH * kH;
-  float* gW3 = gb2 + kH;
-  float* gb3 = gW3 + kOut * kH;
-  hipLaunchKernelGGL(k_mse, dim3(nblk(B)), dim3(256), 0, st, w.O, w.Y, w.M, B, kOut, inv_count,
-                     w.dO, w.lossb);
-  hipLaunchKernelGGL(k_lin_bwd_w, dim3(nblk(kOut * kH + kOut)), dim3(256), 0, st, w.dO, w.H2, B,
-                     kOut, kH, gW3, gb3);
-  hipLaunchKernelGGL(k_lin_bwd_x, dim3(nblk(long(B) * kH)), dim3(256), 0, st, w.dO, B, kOut, n.W3,
-                     kH, w.H2, w.dH2);
-  hipLaunchKernelGGL(k_lin_bwd_w, dim3(nblk(kH * kH + kH)), dim3(256), 0, st, w.dH2, w.H1, B, kH,
-                     kH, gW2, gb2);
-  hipLaunchKernelGGL(k_lin_bwd_x, dim3(nblk(long(B) * kH)), dim3(256), 0, st, w.dH2, B, kH, n.W2,
-                     kH, w.H1, w.dH1);
-  hipLaunchKernelGGL(k_lin_bwd_w, dim3(nblk(kH * kIn + kH)), dim3(256), 0, st, w.dH1, w.X, B, kH,
-                     kIn, gW1, gb1);
-  hipLaunchKernelGGL(k_sum, dim3(1), dim3(256), 0, st, w.lossb, B, w.loss);
+// workgroups (parts) of a minibatch of B samples
+inline int step_parts(int B) { return std::min(kMaxParts, (B + kS - 1) / kS); }
+
+// gradient of the masked MSE into G, summed squared error added to loss; with
+// m: one Adam step of P
+void step(const float* X, const float* Y, const float* M, const int* idx, int B, float inv_count,
+          float* P, float* part, float* lossb, float* G, float* loss, float* m, float* v, Adam ad,
+          hipStream_t st) {
+  const int nw = step_parts(B);
+  hipLaunchKernelGGL(k_mlp_step, dim3(nw), dim3(kStep), 0, st, P, X, Y, M, idx, B, inv_count, part,
+                     lossb);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((kP + 255) / 256), dim3(256), 0, st, part, nw, lossb, G,
+                     loss, P, m, v, ad);
 }
 
 float mask_count(const float* M, long n) {
@@ -326,14 +428,17 @@ extern "C" ltmp2_status ltmp2_mlp_forward(const float* params, const float* X, i
   if (!params || !X || !Yout || n < 1) return mfail(LTMP2_EINVAL, "bad arguments");
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   Work w;
-  if (!w.init(n)) return mfail(LTMP2_ENOMEM, "device allocation failed");
-  if (hipMemcpyAsync(w.P, params, kP * sizeof(float), hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(w.X, X, size_t(n) * kIn * sizeof(float), hipMemcpyHostToDevice, st) !=
+  float *P, *Xd, *H1, *H2, *O;
+  if (!w.init({{&P, kP}, {&Xd, size_t(n) * kIn}, {&H1, size_t(n) * kH}, {&H2, size_t(n) * kH},
+               {&O, size_t(n) * kOut}}))
+    return mfail(LTMP2_ENOMEM, "device allocation failed");
+  if (hipMemcpyAsync(P, params, kP * sizeof(float), hipMemcpyHostToDevice, st) != hipSuccess ||
+      hipMemcpyAsync(Xd, X, size_t(n) * kIn * sizeof(float), hipMemcpyHostToDevice, st) !=
           hipSuccess)
     return mfail(LTMP2_EDEVICE, "copy failed");
-  forward(w, n, st);
+  forward(P, Xd, n, H1, H2, O, st);
   if (hipGetLastError() != hipSuccess) return mfail(LTMP2_EDEVICE, "launch failed");
-  if (hipMemcpyAsync(Yout, w.O, size_t(n) * kOut * sizeof(float), hipMemcpyDeviceToHost, st) !=
+  if (hipMemcpyAsync(Yout, O, size_t(n) * kOut * sizeof(float), hipMemcpyDeviceToHost, st) !=
           hipSuccess ||
       hipStreamSynchronize(st) != hipSuccess)
     return mfail(LTMP2_EDEVICE, "copy back failed");
@@ -391,15 +496,7 @@ extern "C" ltmp2_status ltmp2_mlp_forward_noalloc(const float* params_dev, const
   float* h = scratch_on_current_device(err);
   if (!h) return mfail(LTMP2_EDEVICE, err);
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
-  Net net = unpack(params_dev);
-  float* h1 = h;
-  float* h2 = h + size_t(kNoAllocRows) * kH;
-  hipLaunchKernelGGL(k_lin_fwd, dim3(nblk(long(n) * kH)), dim3(256), 0, st, X_dev, n, kIn,
-                     net.W1, net.b1, kH, 1, h1);
-  hipLaunchKernelGGL(k_lin_fwd, dim3(nblk(long(n) * kH)), dim3(256), 0, st, h1, n, kH, net.W2,
-                     net.b2, kH, 1, h2);
-  hipLaunchKernelGGL(k_lin_fwd, dim3(nblk(long(n) * kOut)), dim3(256), 0, st, h2, n, kH, net.W3,
-                     net.b3, kOut, 0, Y_dev);
+  forward(params_dev, X_dev, n, h, h + size_t(kNoAllocRows) * kH, Y_dev, st);
   if (hipGetLastError() != hipSuccess) return mfail(LTMP2_EDEVICE, "launch failed");
   return LTMP2_OK;
 }
@@ -412,20 +509,23 @@ extern "C" ltmp2_status ltmp2_mlp_grad(const float* params, const float* X, cons
   if (!(cnt > 0)) return mfail(LTMP2_EINVAL, "empty mask");
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   Work w;
-  if (!w.init(n)) return mfail(LTMP2_ENOMEM, "device allocation failed");
+  float *P, *G, *Xd, *Yd, *Md, *part, *lossb, *ld;
+  const int nw = step_parts(n);
+  if (!w.init({{&P, kP}, {&G, kP}, {&Xd, size_t(n) * kIn}, {&Yd, size_t(n) * kOut},
+               {&Md, size_t(n) * kOut}, {&part, size_t(nw) * kP}, {&lossb, nw}, {&ld, 1}}))
+    return mfail(LTMP2_ENOMEM, "device allocation failed");
   const size_t bo = size_t(n) * kOut * sizeof(float);
-  if (hipMemcpyAsync(w.P, params, kP * sizeof(float), hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(w.X, X, size_t(n) * kIn * sizeof(float), hipMemcpyHostToDevice, st) ||
-      hipMemcpyAsync(w.Y, Y, bo, hipMemcpyHostToDevice, st) ||
-      hipMemcpyAsync(w.M, M, bo, hipMemcpyHostToDevice, st) ||
-      hipMemsetAsync(w.loss, 0, sizeof(float), st))
+  if (hipMemcpyAsync(P, params, kP * sizeof(float), hipMemcpyHostToDevice, st) != hipSuccess ||
+      hipMemcpyAsync(Xd, X, size_t(n) * kIn * sizeof(float), hipMemcpyHostToDevice, st) ||
+      hipMemcpyAsync(Yd, Y, bo, hipMemcpyHostToDevice, st) ||
+      hipMemcpyAsync(Md, M, bo, hipMemcpyHostToDevice, st) ||
+      hipMemsetAsync(ld, 0, sizeof(float), st))
     return mfail(LTMP2_EDEVICE, "copy failed");
-  forward(w, n, st);
-  backward(w, n, 1.f / cnt, st);
+  step(Xd, Yd, Md, nullptr, n, 1.f / cnt, P, part, lossb, G, ld, nullptr, nullptr, Adam{}, st);
   if (hipGetLastError() != hipSuccess) return mfail(LTMP2_EDEVICE, "launch failed");
   float l = 0.f;
-  if (hipMemcpyAsync(grad, w.G, kP * sizeof(float), hipMemcpyDeviceToHost, st) ||
-      hipMemcpyAsync(&l, w.loss, sizeof(float), hipMemcpyDeviceToHost, st) ||
+  if (hipMemcpyAsync(grad, G, kP * sizeof(float), hipMemcpyDeviceToHost, st) ||
+      hipMemcpyAsync(&l, ld, sizeof(float), hipMemcpyDeviceToHost, st) ||
       hipStreamSynchronize(st))
     return mfail(LTMP2_EDEVICE, "copy back failed");
   if (loss) *loss = l / cnt;
@@ -440,61 +540,54 @@ extern "C" ltmp2_status ltmp2_mlp_train(float* params, const float* X, const flo
   batch = std::min(batch, n);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   Work w;
-  float *dX = nullptr, *dY = nullptr, *dM = nullptr, *m1 = nullptr, *m2 = nullptr;
-  int* didx = nullptr;
-  if (!w.init(batch) || !w.alloc(&dX, size_t(n) * kIn) || !w.alloc(&dY, size_t(n) * kOut) ||
-      !w.alloc(&dM, size_t(n) * kOut) || !w.alloc(&m1, kP) || !w.alloc(&m2, kP) ||
-      !w.alloc(reinterpret_cast<float**>(&didx), batch))
+  float *P, *G, *dX, *dY, *dM, *m1, *m2, *part, *lossb, *dloss, *didx;
+  const int nw = step_parts(batch);
+  if (!w.init({{&P, kP}, {&G, kP}, {&dX, size_t(n) * kIn}, {&dY, size_t(n) * kOut},
+               {&dM, size_t(n) * kOut}, {&m1, kP}, {&m2, kP}, {&part, size_t(nw) * kP},
+               {&lossb, nw}, {&dloss, 1}, {&didx, n}}))
     return mfail(LTMP2_ENOMEM, "device allocation failed");
-  if (hipMemcpyAsync(w.P, params, kP * sizeof(float), hipMemcpyHostToDevice, st) ||
+  if (hipMemcpyAsync(P, params, kP * sizeof(float), hipMemcpyHostToDevice, st) ||
       hipMemcpyAsync(dX, X, size_t(n) * kIn * sizeof(float), hipMemcpyHostToDevice, st) ||
       hipMemcpyAsync(dY, Y, size_t(n) * kOut * sizeof(float), hipMemcpyHostToDevice, st) ||
       hipMemcpyAsync(dM, M, size_t(n) * kOut * sizeof(float), hipMemcpyHostToDevice, st) ||
       hipMemsetAsync(m1, 0, kP * sizeof(float), st) || hipMemsetAsync(m2, 0, kP * sizeof(float), st))
     return mfail(LTMP2_EDEVICE, "copy failed");
+  // unmasked outputs per sample (a minibatch's loss is a mean over them)
+  std::vector<double> rows(n, 0.0);
+  for (int b = 0; b < n; ++b)
+    for (int k = 0; k < kOut; ++k) rows[b] += M[size_t(b) * kOut + k];
   uint64_t s = seed;
   std::vector<int> perm(n);
-  std::vector<float> mrow(size_t(batch) * kOut);
-  long step = 0;
+  long nstep = 0;
   const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
   for (int ep = 0; ep < epochs; ++ep) {
     for (int k = 0; k < n; ++k) perm[k] = k;
     for (int k = n - 1; k > 0; --k) std::swap(perm[k], perm[int(uniform01(s) * (k + 1))]);
     // cosine learning-rate schedule
     const float lre = lr * 0.5f * (1.f + std::cos(float(M_PI) * ep / epochs));
-    if (hipMemsetAsync(w.loss, 0, sizeof(float), st)) return mfail(LTMP2_EDEVICE, "memset");
+    // the epoch's order in one copy; the copy back of the loss below keeps
+    // perm unchanged until the stream is done with it
+    if (hipMemsetAsync(dloss, 0, sizeof(float), st) ||
+        hipMemcpyAsync(didx, perm.data(), size_t(n) * sizeof(int), hipMemcpyHostToDevice, st))
+      return mfail(LTMP2_EDEVICE, "copy failed");
     double epoch_count = 0.0;
     for (int b0 = 0; b0 + batch <= n; b0 += batch) {
-      if (hipMemcpyAsync(didx, perm.data() + b0, batch * sizeof(int), hipMemcpyHostToDevice, st))
-        return mfail(LTMP2_EDEVICE, "copy failed");
       double cnt = 0.0;
-      for (int b = 0; b < batch; ++b)
-        for (int k = 0; k < kOut; ++k) cnt += M[size_t(perm[b0 + b]) * kOut + k];
+      for (int b = 0; b < batch; ++b) cnt += rows[perm[b0 + b]];
       epoch_count += cnt;
-      hipLaunchKernelGGL(k_gather, dim3(nblk(long(batch) * kIn)), dim3(256), 0, st, dX, didx, batch,
-                         kIn, w.X);
-      hipLaunchKernelGGL(k_gather, dim3(nblk(long(batch) * kOut)), dim3(256), 0, st, dY, didx, batch,
-                         kOut, w.Y);
-      hipLaunchKernelGGL(k_gather, dim3(nblk(long(batch) * kOut)), dim3(256), 0, st, dM, didx, batch,
-                         kOut, w.M);
-      forward(w, batch, st);
-      backward(w, batch, float(1.0 / cnt), st);
-      ++step;
-      const float bc1 = 1.f - std::pow(b1, float(step)), bc2 = 1.f - std::pow(b2, float(step));
-      hipLaunchKernelGGL(k_adam, dim3(nblk(kP)), dim3(256), 0, st, w.P, w.G, m1, m2, kP, lre, b1,
-                         b2, eps, bc1, bc2);
-      // hipMemcpyAsync of the index list above reads host memory that the next
-      // iteration overwrites; keep the stream ordered with the host
-      if (hipStreamSynchronize(st)) return mfail(LTMP2_EDEVICE, "training step failed");
+      ++nstep;
+      const float bc1 = 1.f - std::pow(b1, float(nstep)), bc2 = 1.f - std::pow(b2, float(nstep));
+      step(dX, dY, dM, reinterpret_cast<const int*>(didx) + b0, batch, float(1.0 / cnt), P, part,
+           lossb, G, dloss, m1, m2, Adam{lre, b1, b2, eps, bc1, bc2}, st);
     }
     float l = 0.f;
-    if (hipMemcpyAsync(&l, w.loss, sizeof(float), hipMemcpyDeviceToHost, st) ||
+    if (hipMemcpyAsync(&l, dloss, sizeof(float), hipMemcpyDeviceToHost, st) ||
         hipStreamSynchronize(st))
       return mfail(LTMP2_EDEVICE, "copy back failed");
     if (loss_hist) loss_hist[ep] = float(l / epoch_count);
   }
   if (hipGetLastError() != hipSuccess) return mfail(LTMP2_EDEVICE, "launch failed");
-  if (hipMemcpyAsync(params, w.P, kP * sizeof(float), hipMemcpyDeviceToHost, st) ||
+  if (hipMemcpyAsync(params, P, kP * sizeof(float), hipMemcpyDeviceToHost, st) ||
       hipStreamSynchronize(st))
     return mfail(LTMP2_EDEVICE, "copy back failed");
   return LTMP2_OK;
