@@ -44,6 +44,7 @@ struct ltmp2_ctx {
   int* d_ckx = nullptr;
   int* d_wq = nullptr;
   signed char* d_wsgn = nullptr;
+  int* d_wx = nullptr;
   int* d_gdesc = nullptr;
   int* d_pairs = nullptr;
   int* d_cols = nullptr;          // [ncol] columns of the pair transforms (PairCell)

@@ -8,6 +8,7 @@
 #include "../../include/ltmp2.h"
 #include "kernels_fft.hpp"
 #include "kernels_pair.hpp"
+#include "kernels_wstates.hpp"
 #include "modes.h"
 
 namespace ltmp2 {
@@ -30,8 +31,9 @@ struct GridOps {
   ltmp2_status (*chi_cols)(const cplx<T>* chihat, long ld, const int* gdesc, int ng, int nh,
                            const double* v, int kmax, double dV, double* pd,
                            cplx<double>* chi_out, ShellBins bins, hipStream_t st);
+  // wx: index table of the window wstates_window(n, sc.kmax) (null if none)
   ltmp2_status (*wstates)(const T* P, int npw, const int* wq, const signed char* wsgn,
-                          SphereCols sc, int nitems, double scale, T* w, long ld,
+                          const int* wx, SphereCols sc, int nitems, double scale, T* w, long ld,
                           hipStream_t st);
   // pair transforms of one block of outer vectors of a cell
   ltmp2_status (*pair)(const PairCell& pc, hipStream_t st);

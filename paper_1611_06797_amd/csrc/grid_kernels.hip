@@ -160,9 +160,26 @@ ltmp2_status hartree(const cplx<T>* h, long ld, const int* gdesc, int ng, const 
   return by_opt<HartreeF<T>::template F>(ng, h, ld, gdesc, ng, v, kmax, dV, g0, gb, pdh, st);
 }
 
+template <class T, int K>
+ltmp2_status wstates_window_launch(const T* P, int npw, const int* wx, int nitems, double scale,
+                                   T* w, long ld, hipStream_t st) {
+  using W = WstShape<T, N, K>;
+  return launch_nt(k_wstates_real<T, N, K>, dim3(unsigned(2L * nitems / W::F)), W::NT, W::lds(npw),
+                   st, P, npw, wx, scale, w, ld);
+}
+
 template <class T>
-ltmp2_status wstates(const T* P, int npw, const int* wq, const signed char* wsgn, SphereCols sc,
-                     int nitems, double scale, T* w, long ld, hipStream_t st) {
+ltmp2_status wstates(const T* P, int npw, const int* wq, const signed char* wsgn, const int* wx,
+                     SphereCols sc, int nitems, double scale, T* w, long ld, hipStream_t st) {
+  constexpr int ko = korb_win(N), kl = ko < 2 ? ko : ko - 1;
+  // (a set far from a sphere can be too large for shared memory next to the field)
+  if (wx) {
+    const int win = wstates_window(N, sc.kmax);
+    if (win == ko && WstShape<T, N, ko>::lds(npw) <= kLdsCap)
+      return wstates_window_launch<T, ko>(P, npw, wx, nitems, scale, w, ld, st);
+    if (win == kl && WstShape<T, N, kl>::lds(npw) <= kLdsCap)
+      return wstates_window_launch<T, kl>(P, npw, wx, nitems, scale, w, ld, st);
+  }
   // the largest slab tile that lets four workgroups share a CU, unless two
   // workgroups per CU would allow more than twice that tile
   const int nk = 2 * sc.kmax + 1;
@@ -173,18 +190,8 @@ ltmp2_status wstates(const T* P, int npw, const int* wq, const signed char* wsgn
   };
   const int s4 = tile(kLdsQuarter), s2 = tile(kLdsHalf);
   const int sx = 2 * s4 >= s2 ? s4 : s2;
-  const size_t lds = inv_lds_bytes<T>(N, nk, sx);
-  // orbital spheres at the alias-free window and one below run kernels
-  // compiled for that kmax (no per-element branches in the y and z stages)
-  constexpr int ko = korb_win(N);
-  if (sc.kmax == ko)
-    return launch(k_wstates<T, N, ko>, dim3(nitems), lds, st, P, npw, wq, wsgn, sc, sx, scale, w,
-                  ld);
-  if constexpr (ko > 1)
-    if (sc.kmax == ko - 1)
-      return launch(k_wstates<T, N, ko - 1>, dim3(nitems), lds, st, P, npw, wq, wsgn, sc, sx,
-                    scale, w, ld);
-  return launch(k_wstates<T, N>, dim3(nitems), lds, st, P, npw, wq, wsgn, sc, sx, scale, w, ld);
+  return launch(k_wstates<T, N>, dim3(nitems), inv_lds_bytes<T>(N, nk, sx), st, P, npw, wq, wsgn,
+                sc, sx, scale, w, ld);
 }
 
 // Kept-set instance of the pair kernels for a cell (-1: none holds it).
@@ -278,7 +285,7 @@ ltmp2_status plane_order(const T* in, long ld, int nocc, T* out, hipStream_t st)
   template ltmp2_status chi_cols<T>(const cplx<T>*, long, const int*, int, int, const double*, \
                                     int, double, double*, cplx<double>*, ShellBins,            \
                                     hipStream_t);                                              \
-  template ltmp2_status wstates<T>(const T*, int, const int*, const signed char*, SphereCols,   \
+  template ltmp2_status wstates<T>(const T*, int, const int*, const signed char*, const int*, SphereCols, \
                                    int, double, T*, long, hipStream_t);                        \
   template ltmp2_status pair<T>(const PairCell&, hipStream_t);                                 \
   template ltmp2_status pair_multi<T>(const PairCell*, const long*, int, long, int, int,       \

@@ -245,25 +245,21 @@ __global__ __launch_bounds__(kThreads) void k_hartree(const cplx<T>* __restrict_
 }
 
 // ---------------------------------------------------------------------------
-// Transformed states on the grid (step (iii)):
-//   w_j^{(G')}(r) = Omega^-1/2 sum_G W_j(G) e^{iG.r},
-// with W_j(G) rebuilt from the real-basis product P = C Psi_v:
-//   P[(g, j, 0)][q] = sum_a Re C_ja B[a][q],  P[(g, j, 1)][q] = sum_a Im C_ja B[a][q],
-// where B[a][q] holds Re c_a(0), Re c_a(G_k), Im c_a(G_k) for the half sphere.
-// W_j(G) is gathered from P where the x stage needs it.
+// Transformed states on the grid where the orbital sphere is beyond the window
+// of kernels_wstates.hpp (the caller's grid aliases; see there for P and w):
+// both fields as one complex transform, W_j(G) gathered from P where the x
+// stage needs it.
 // Entry e of the sphere (column order) uses wq[e] = q_re | (q_im + 1) << 16
 // and the sign s = +1 for G_k, -1 for -G_k (c_a(-G) = conj c_a(G)):
 //   W(G) = (P_re[q_re] - s P_im[q_im]) + i (P_im[q_re] + s P_re[q_im]).
-// w is stored as two real fields per state, [item][2][ld], in the plane order
-// of the pair transforms (r = (z N + x) N + y).
-template <class T, int N, int KO = -1>
+template <class T, int N>
 __global__ __launch_bounds__(kThreads) void k_wstates(const T* __restrict__ P, int npw,
                                                       const int* __restrict__ wq,
                                                       const signed char* __restrict__ wsgn,
                                                       SphereCols sc, int sx, double scale,
                                                       T* __restrict__ w, long ld) {
   extern __shared__ __align__(16) char smem[];
-  const int nk = 2 * (KO >= 0 ? KO : sc.kmax) + 1;
+  const int nk = 2 * sc.kmax + 1;
   SlabLds<T> L = inv_lds<T>(smem, N, nk, sx);
   fill_twiddles<T, 1, N>(L.tw);
   const long item = blockIdx.x;
@@ -288,7 +284,7 @@ __global__ __launch_bounds__(kThreads) void k_wstates(const T* __restrict__ P, i
     o[0] = T(scale) * v.x;
     o[ld] = T(scale) * v.y;
   };
-  inverse_sphere<T, N, 1, KO>(cf, st, 1, sc.kmax, sx, sc.ncol, sc.cdesc, sc.cstart, sc.ckx, L);
+  inverse_sphere<T, N, 1>(cf, st, 1, sc.kmax, sx, sc.ncol, sc.cdesc, sc.cstart, sc.ckx, L);
 }
 
 }  // namespace ltmp2

@@ -493,6 +493,20 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
       wsgn[e] = -1;
     }
   }
+  // the same by (kx, kz >= 0, ky) for the kernels of a sphere window
+  std::vector<int> wx;
+  const int kwx = wstates_window(c->n, ko);
+  if (kwx >= 0) {
+    const int nkw = 2 * kwx + 1, slots = (kwx + 1) * nkw;
+    wx.assign(size_t(nkw) * slots, (c->npw + 1) / 2);
+    for (int e = 0; e < c->npw; ++e) {
+      const int i = order[e], x = miller[3 * i], y = miller[3 * i + 1], z = miller[3 * i + 2];
+      if (z < 0) continue;
+      const int q = wq[e] & 0xffff, s = z * nkw + y + kwx;
+      wx[size_t(x + kwx) * slots + s] =
+          ((q + 1) / 2) | int(wsgn[e] < 0 ? 0x80000000u : 0u);
+    }
+  }
   // coefficients in column order, and the real basis of the virtual ones
   std::vector<double> coef_col(2 * size_t(c->nst) * c->npw);
   c->ldbpw = (c->npw + 3) / 4 * 4;  // 16-byte aligned rows
@@ -602,7 +616,8 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
   ltmp2_status s;
   if ((s = upload(c, &c->d_cdesc, cdesc)) || (s = upload(c, &c->d_cstart, cstart)) ||
       (s = upload(c, &c->d_ckx, ckx)) || (s = upload(c, &c->d_wq, wq)) ||
-      (s = upload(c, &c->d_wsgn, wsgn)) || (s = upload(c, &c->d_gdesc, gdesc)) ||
+      (s = upload(c, &c->d_wsgn, wsgn)) ||
+      (!wx.empty() && (s = upload(c, &c->d_wx, wx))) || (s = upload(c, &c->d_gdesc, gdesc)) ||
       (s = upload(c, &c->d_pairs, pairs)) || (s = upload(c, &c->d_cols, cols)) ||
       (s = upload(c, &c->d_vm2, vm2)) || (s = upload(c, &c->d_v, v)) ||
       (s = upload(c, &c->d_fo, fo)) || (s = upload(c, &c->d_fv, fv)))
@@ -791,8 +806,9 @@ ltmp2_status block_prepare_t(ltmp2_ctx* c, int itau, int g0, int gb) {
   if (s) return fail(c, s, "transformed-state GEMM launch failed");
   {
     StageTimer tm(c, 4);
-    s = ops->wstates(static_cast<const T*>(c->d_P), c->npw, c->d_wq, c->d_wsgn, c->sc, gb * c->no,
-                     1.0 / std::sqrt(c->omega), static_cast<T*>(c->d_w), c->nrp, c->stream);
+    s = ops->wstates(static_cast<const T*>(c->d_P), c->npw, c->d_wq, c->d_wsgn, c->d_wx, c->sc,
+                     gb * c->no, 1.0 / std::sqrt(c->omega), static_cast<T*>(c->d_w), c->nrp,
+                     c->stream);
   }
   if (s) return fail(c, s, "transformed-state launch failed");
   return LTMP2_OK;

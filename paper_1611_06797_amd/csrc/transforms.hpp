@@ -100,6 +100,14 @@ __host__ __device__ constexpr int kwin(int n) { return (n - 1) / 3; }
 // auxiliary window kwin(N), an alias-free grid allows k_orb <= korb_win(N).
 __host__ __device__ constexpr int korb_win(int n) { return (n - 1 - kwin(n)) / 2; }
 
+// Sphere window of the transformed-state kernels compiled for one (see
+// kernels_wstates.hpp): korb_win or one below; smaller spheres run in the
+// latter, -1: none holds it (the caller's grid aliases).
+__host__ __device__ constexpr int wstates_window(int n, int kmax) {
+  const int ko = korb_win(n);
+  return kmax > ko ? -1 : (kmax == ko || ko < 2) ? ko : ko - 1;
+}
+
 // Largest slab tile d <= cap that divides n (tiles are 1..6, 8, 9, 10, 12).
 __host__ __device__ constexpr int slab_tile_at_most(int n, int cap) {
   for (int d = cap < 12 ? cap : 12; d > 1; --d)
@@ -252,13 +260,11 @@ __device__ __forceinline__ void forward_pruned(const Load& ld, int nf_active, in
 // group x2 = planes x2 + M xs): per (ky, kz) slot and residue q < sx,
 // Z(q) = sum_{kx = q mod sx} c(kx) w_N^{kx x2} (zero for slots outside the
 // sphere), then a length-sx FFT over q gives the group's planes.
-// KO >= 0 fixes kmax = KO at compile time (see korb_win).
-template <class T, int N, int NF, int KO = -1, class Coef, class Store>
+template <class T, int N, int NF, class Coef, class Store>
 __device__ inline void inverse_sphere(const Coef& cf, const Store& st, int nf_active,
-                                      int kmax_rt, int sx, int ncol, const int* cdesc,
+                                      int kmax, int sx, int ncol, const int* cdesc,
                                       const int* cstart, const int* ckx, const SlabLds<T>& L) {
   constexpr int R = slab_row(N);
-  const int kmax = KO >= 0 ? KO : kmax_rt;
   const int nk = 2 * kmax + 1, nc = nk * nk, M = N / sx;
   const int tid = threadIdx.x;
   for (int s = tid; s < nc; s += kThreads) L.cmap[s] = 0;
