@@ -24,10 +24,12 @@ template <class T>
 struct GridOps {
   ltmp2_status (*orbitals)(const cplx<double>* coef, int nstates, int npw, SphereCols sc,
                            double scale, T* psi, long ld, hipStream_t st);
-  ltmp2_status (*overlap)(const T* psi, long ld, int no, int nv, const int* gdesc, int nh,
-                          int kmax, double dV, cplx<T>* nd, hipStream_t st);
-  ltmp2_status (*chi_rows)(const T* chi, long ld, int nr, const int* gdesc, int nh, int kmax,
-                           double dV, cplx<T>* chihat, hipStream_t st);
+  ltmp2_status (*overlap)(const T* psi, long ld, int no, int nv, const int* cols, int ncol,
+                          const int* gdesc, int nh, int kmax, double dV, cplx<T>* nd,
+                          hipStream_t st);
+  ltmp2_status (*chi_rows)(const T* chi, long ld, int nr, const int* cols, int ncol,
+                           const int* gdesc, int nh, int kmax, double dV, cplx<T>* chihat,
+                           hipStream_t st);
   ltmp2_status (*chi_cols)(const cplx<T>* chihat, long ld, const int* gdesc, int ng, int nh,
                            const double* v, int kmax, double dV, double* pd,
                            cplx<double>* chi_out, ShellBins bins, hipStream_t st);

@@ -83,45 +83,6 @@ ltmp2_status orbitals(const cplx<double>* coef, int nstates, int npw, SphereCols
 }
 
 template <class T>
-struct OverlapF {
-  template <int OPT>
-  struct F {
-    static ltmp2_status go(const T* psi, long ld, int no, int nv, const int* gdesc, int nh,
-                           int kmax, double dV, cplx<T>* nd, hipStream_t st) {
-      constexpr int NF = 4;
-      const int nk = 2 * kmax + 1, sx = choose_sx_fwd<T>(nk);
-      return launch(k_overlap<T, N, NF, OPT>, dim3((no + NF - 1) / NF, nv),
-                    fwd_lds_bytes<T>(N, nk, sx), st, psi, ld, no, gdesc, nh, kmax, sx, dV, nd);
-    }
-  };
-};
-template <class T>
-ltmp2_status overlap(const T* psi, long ld, int no, int nv, const int* gdesc, int nh, int kmax,
-                     double dV, cplx<T>* nd, hipStream_t st) {
-  return by_opt<OverlapF<T>::template F>(nh, psi, ld, no, nv, gdesc, nh, kmax, dV, nd, st);
-}
-
-template <class T>
-struct ChiRowsF {
-  template <int OPT>
-  struct F {
-    static ltmp2_status go(const T* chi, long ld, int nr, const int* gdesc, int nh, int kmax,
-                           double dV, cplx<T>* chihat, hipStream_t st) {
-      constexpr int NF = 2;
-      const int nk = 2 * kmax + 1, sx = choose_sx_fwd<T>(nk);
-      return launch(k_chi_rows<T, N, NF, OPT>, dim3((nr + NF - 1) / NF),
-                    fwd_lds_bytes<T>(N, nk, sx), st, chi, ld, nr, gdesc, nh, kmax, sx, dV,
-                    chihat);
-    }
-  };
-};
-template <class T>
-ltmp2_status chi_rows(const T* chi, long ld, int nr, const int* gdesc, int nh, int kmax, double dV,
-                      cplx<T>* chihat, hipStream_t st) {
-  return by_opt<ChiRowsF<T>::template F>(nh, chi, ld, nr, gdesc, nh, kmax, dV, chihat, st);
-}
-
-template <class T>
 struct ChiColsF {
   template <int OPT>
   struct F {
@@ -221,6 +182,29 @@ size_t pair_lds(int ncol) {
   return pair_lds_bytes(sizeof(T), N, KM, ns, ncol);
 }
 
+template <class T, bool OVERLAP>
+ltmp2_status real_forward(const T* a, long ld, int nocc, long items, const int* cols, int ncol,
+                          const int* gdesc, int nh, int kmax, double scale, cplx<T>* out,
+                          hipStream_t st) {
+  return with_instance(kmax, [&](auto km) -> ltmp2_status {
+    constexpr int KM = decltype(km)::value, NT = pair_threads(sizeof(T), N, KM);
+    if (ncol < 1 || ncol > pair_cols_max(KM)) return LTMP2_EINVAL;
+    const size_t lds = std::max(pair_lds<T, KM>(ncol), sizeof(T) * (2 * KM + 1) * ncol);
+    return launch_nt(k_real_forward<T, N, KM, OVERLAP>, dim3(unsigned((items + 7) / 8 * 8)), NT,
+                     lds, st, a, ld, nocc, items, cols, ncol, gdesc, nh, kmax, scale, out);
+  });
+}
+template <class T>
+ltmp2_status overlap(const T* psi, long ld, int no, int nv, const int* cols, int ncol,
+                     const int* gdesc, int nh, int kmax, double dV, cplx<T>* nd, hipStream_t st) {
+  return real_forward<T, true>(psi, ld, no, long(no) * nv, cols, ncol, gdesc, nh, kmax, dV, nd, st);
+}
+template <class T>
+ltmp2_status chi_rows(const T* chi, long ld, int nr, const int* cols, int ncol, const int* gdesc,
+                      int nh, int kmax, double dV, cplx<T>* chihat, hipStream_t st) {
+  return real_forward<T, false>(chi, ld, 1, nr, cols, ncol, gdesc, nh, kmax, dV, chihat, st);
+}
+
 // Launches that split by cutoff shell run an instance with that epilogue
 // compiled in; the others run one without it (fewer live registers).
 template <class T>
@@ -276,17 +260,17 @@ ltmp2_status plane_order(const T* in, long ld, int nocc, T* out, hipStream_t st)
 // Explicit instantiation in both compilation passes, so the device pass
 // instantiates every kernel the host launchers reference.
 #define LTMP2_INST(T)                                                                          \
-  template ltmp2_status orbitals<T>(const cplx<double>*, int, int, SphereCols, double, T*, long, \
+  template ltmp2_status orbitals<T>(const cplx<double>*, int, int, SphereCols, double, T*, long,\
                                     hipStream_t);                                              \
-  template ltmp2_status overlap<T>(const T*, long, int, int, const int*, int, int, double,     \
-                                   cplx<T>*, hipStream_t);                                     \
-  template ltmp2_status chi_rows<T>(const T*, long, int, const int*, int, int, double, cplx<T>*, \
-                                    hipStream_t);                                              \
+  template ltmp2_status overlap<T>(const T*, long, int, int, const int*, int, const int*, int, \
+                                   int, double, cplx<T>*, hipStream_t);                        \
+  template ltmp2_status chi_rows<T>(const T*, long, int, const int*, int, const int*, int, int,\
+                                    double, cplx<T>*, hipStream_t);                            \
   template ltmp2_status chi_cols<T>(const cplx<T>*, long, const int*, int, int, const double*, \
                                     int, double, double*, cplx<double>*, ShellBins,            \
                                     hipStream_t);                                              \
-  template ltmp2_status wstates<T>(const T*, int, const int*, const signed char*, const int*, SphereCols, \
-                                   int, double, T*, long, hipStream_t);                        \
+  template ltmp2_status wstates<T>(const T*, int, const int*, const signed char*, const int*,  \
+                                   SphereCols, int, double, T*, long, hipStream_t);            \
   template ltmp2_status pair<T>(const PairCell&, hipStream_t);                                 \
   template ltmp2_status pair_multi<T>(const PairCell*, const long*, int, long, int, int,       \
                                       hipStream_t);                                            \

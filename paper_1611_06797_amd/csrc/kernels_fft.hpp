@@ -34,92 +34,6 @@ __global__ __launch_bounds__(kThreads) void k_orbitals(const cplx<double>* __res
 }
 
 // ---------------------------------------------------------------------------
-// Overlap densities (step (i)): n_aj(G) = dV sum_r psi_a(r) psi_j(r) e^{-iG.r}
-// for G in the half set H.  Block (jblock, a); NF occupied j per block.
-//   nd: [n_vir][n_h][n_occ] complex
-template <class T, int N, int NF, int OPT>
-__global__ __launch_bounds__(kThreads) void k_overlap(const T* __restrict__ psi, long ld, int nocc,
-                                                      const int* __restrict__ gdesc_all, int nh,
-                                                      int kmax, int sx, double dV,
-                                                      cplx<T>* __restrict__ nd) {
-  extern __shared__ __align__(16) char smem[];
-  const int nk = 2 * kmax + 1;
-  SlabLds<T> L = fwd_lds<T>(smem, N, nk, sx);
-  fill_twiddles<T, -1, N>(L.tw);
-  const int j0 = blockIdx.x * NF;
-  const int a = blockIdx.y;
-  const int nf = min(NF, nocc - j0);
-  const T* pa = psi + long(nocc + a) * ld;
-  const T* pj = psi + long(j0) * ld;
-  int gd[OPT];
-  cplx<T> acc[NF][OPT];
-#pragma unroll
-  for (int t = 0; t < OPT; ++t) {
-    const int o = threadIdx.x + t * kThreads;
-    gd[t] = (o < nh) ? gdesc_all[o] : 0;
-#pragma unroll
-    for (int f = 0; f < NF; ++f) acc[f][t] = {T(0), T(0)};
-  }
-  __syncthreads();
-  auto ld_ = [&](int f, int x, int y, int z) {
-    const long r = (x * N + z) * N + y;
-    return cplx<T>{pa[r] * pj[f * ld + r], T(0)};
-  };
-  forward_pruned<T, -1, N, NF, OPT>(ld_, nf, kmax, sx, gd, nh, acc, L);
-#pragma unroll
-  for (int t = 0; t < OPT; ++t) {
-    const int o = threadIdx.x + t * kThreads;
-    if (o < nh) {
-#pragma unroll
-      for (int f = 0; f < NF; ++f)
-        if (f < nf)
-          nd[(long(a) * nh + o) * nocc + j0 + f] = {T(dV) * acc[f][t].x, T(dV) * acc[f][t].y};
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// First pass of the double transform of chi (rows): for NF rows r,
-//   chihat(r, G') = dV sum_r' chi(r, r') e^{+iG'.r'},  G' in H.
-//   chi: [n_r][ld] real;  chihat: [n_h][ld] complex (column-major in r)
-template <class T, int N, int NF, int OPT>
-__global__ __launch_bounds__(kThreads) void k_chi_rows(const T* __restrict__ chi, long ld, int nr,
-                                                       const int* __restrict__ gdesc_all, int nh,
-                                                       int kmax, int sx, double dV,
-                                                       cplx<T>* __restrict__ chihat) {
-  extern __shared__ __align__(16) char smem[];
-  const int nk = 2 * kmax + 1;
-  SlabLds<T> L = fwd_lds<T>(smem, N, nk, sx);
-  fill_twiddles<T, 1, N>(L.tw);
-  const int r0 = blockIdx.x * NF;
-  const int nf = min(NF, nr - r0);
-  const T* row = chi + long(r0) * ld;
-  int gd[OPT];
-  cplx<T> acc[NF][OPT];
-#pragma unroll
-  for (int t = 0; t < OPT; ++t) {
-    const int o = threadIdx.x + t * kThreads;
-    gd[t] = (o < nh) ? gdesc_all[o] : 0;
-#pragma unroll
-    for (int f = 0; f < NF; ++f) acc[f][t] = {T(0), T(0)};
-  }
-  __syncthreads();
-  auto ld_ = [&](int f, int x, int y, int z) {
-    return cplx<T>{row[f * ld + (x * N + z) * N + y], T(0)};
-  };
-  forward_pruned<T, 1, N, NF, OPT>(ld_, nf, kmax, sx, gd, nh, acc, L);
-#pragma unroll
-  for (int t = 0; t < OPT; ++t) {
-    const int o = threadIdx.x + t * kThreads;
-    if (o < nh) {
-#pragma unroll
-      for (int f = 0; f < NF; ++f)
-        if (f < nf) chihat[long(o) * ld + r0 + f] = {T(dV) * acc[f][t].x, T(dV) * acc[f][t].y};
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // Second pass (columns) and the Coulomb trace: for G' = H[g],
 //   chi(G, G') = dV sum_r e^{-iG.r} chihat(r, G'),  G in the full set,
 //   pd[g] = v(G') sum_G v(G) |chi(G, G')|^2.

@@ -159,14 +159,31 @@ __device__ inline double field_load<double>(__amdgpu_buffer_rsrc_t rs, unsigned 
   return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0));
 }
 
-// Trigonometric transform of the real field pa pu onto the columns: out[rx]
-// of column threadIdx.x.  Slab by slab, z lines (x, y) into the line buffer
+// First column and number of columns << 16 of each row rz (columns come in
+// ascending (rz, ry) order, ry without gaps).
+template <int NK, int NT>
+__device__ __forceinline__ void row_table(const int* cols, int ncol, int* rows) {
+  for (int r = threadIdx.x; r < NK; r += NT) rows[r] = 0;
+  __syncthreads();
+  for (int c = threadIdx.x; c < ncol; c += NT) {
+    const int rz = cols[c] >> 8;
+    if (c + 1 == ncol || (cols[c + 1] >> 8) != rz) {
+      const int cnt = (cols[c] & 0xff) + 1;
+      rows[rz] = (c + 1 - cnt) | (cnt << 16);
+    }
+  }
+  __syncthreads();
+}
+
+// Trigonometric transform of the real field pa pu (pa alone without PROD) onto
+// the columns: out[rx] of column threadIdx.x.  Slab by slab, z lines (x, y) into the line buffer
 // t1 [SP][nk][R], y lines (x, rz) in place or, in all slabs but the last,
 // into the column buffer t2 [x][ncol]; then x lines per column.  Ends without
 // a barrier: t1 and t2 may be refilled after the caller's next one.
-template <class T, int N, int KM, int NT, int NS>
-__device__ __forceinline__ void line_transform(const T* pa, const T* pu, const PairCell& pc, T* t1,
-                                               T* t2, const int* rows, T (&out)[2 * KM + 1]) {
+template <class T, int N, int KM, int NT, int NS, bool PROD = true>
+__device__ __forceinline__ void line_transform(const T* pa, const T* pu, const int* cols, int ncol,
+                                               T* t1, T* t2, const int* rows,
+                                               T (&out)[2 * KM + 1]) {
   constexpr int R = line_row(N), nk = 2 * KM + 1, SP = N / NS, P = N * N;
   const int tid = threadIdx.x;
   const auto ra = field_rsrc(pa, P * N), ru = field_rsrc(pu, P * N);
@@ -179,13 +196,14 @@ __device__ __forceinline__ void line_transform(const T* pa, const T* pu, const P
       cplx<T> X[N / 2 + 1];
 #pragma unroll
       for (int z = 0; z < N; ++z) a[z] = field_load<T>(ra, r0 + unsigned(z * P * sizeof(T)));
+      if constexpr (PROD)
 #pragma unroll
-      for (int z = 0; z < N; ++z) u[z] = field_load<T>(ru, r0 + unsigned(z * P * sizeof(T)));
+        for (int z = 0; z < N; ++z) u[z] = field_load<T>(ru, r0 + unsigned(z * P * sizeof(T)));
       // all loads of the line are issued before the first product waits (left
       // to itself the compiler spaces them out: 24 grid 37 instead of 25 ns)
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int z = 0; z < N; ++z) v[z] = a[z] * u[z];
+      for (int z = 0; z < N; ++z) v[z] = PROD ? a[z] * u[z] : a[z];
       RFft<T, N>::run(v, X);
       const int xs = l / N;
       T* o = t1 + xs * (nk * R) + (l - xs * N);
@@ -207,7 +225,7 @@ __device__ __forceinline__ void line_transform(const T* pa, const T* pu, const P
       RFft<T, N>::run(v, X);
       if (NS > 1 && s + 1 < NS) {
         const int xs = l / nk, m = rows[l - xs * nk], cnt = m >> 16;
-        T* d = t2 + (s * SP + xs) * pc.ncol + (m & 0xffff);
+        T* d = t2 + (s * SP + xs) * ncol + (m & 0xffff);
         if (cnt > 0) d[0] = X[0].x;
 #pragma unroll
         for (int k = 1; k <= KM; ++k)
@@ -226,14 +244,14 @@ __device__ __forceinline__ void line_transform(const T* pa, const T* pu, const P
     }
     lds_barrier();
   }
-  if (tid < pc.ncol) {
-    const int cd = pc.cols[tid];
+  if (tid < ncol) {
+    const int cd = cols[tid];
     const T* c1 = t1 + (cd >> 8) * R + (cd & 0xff);
     T v[N];
     cplx<T> X[N / 2 + 1];
 #pragma unroll
     for (int x = 0; x < N; ++x)
-      v[x] = (x < N - SP) ? t2[x * pc.ncol + tid] : c1[(x - (N - SP)) * (nk * R)];
+      v[x] = (x < N - SP) ? t2[x * ncol + tid] : c1[(x - (N - SP)) * (nk * R)];
     RFft<T, N>::run(v, X);
     out[0] = X[0].x;
 #pragma unroll
@@ -268,20 +286,7 @@ __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* 
     if constexpr (BINS)
       if (split) sh[k] = pc.shm2[k];
   }
-  if constexpr (NS > 1) {
-    // first column and number of columns of each row rz (columns come in
-    // ascending (rz, ry) order)
-    for (int r = tid; r < nk; r += NT) rows[r] = 0;
-    __syncthreads();
-    for (int c = tid; c < pc.ncol; c += NT) {
-      const int rz = pc.cols[c] >> 8;
-      if (c + 1 == pc.ncol || (pc.cols[c + 1] >> 8) != rz) {
-        const int cnt = (pc.cols[c] & 0xff) + 1;
-        rows[rz] = (c + 1 - cnt) | (cnt << 16);
-      }
-    }
-    __syncthreads();
-  }
+  if constexpr (NS > 1) row_table<nk, NT>(pc.cols, pc.ncol, rows);
   double s = 0.0;
   double sb[kMaxShells] = {};
   const int sg = split ? pc.shell[pc.g0 + gl] : 0;
@@ -290,10 +295,12 @@ __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* 
     const T* ui = w + ((long(gl) * pc.nocc + i) * 2 + part) * pc.ld;
     const T* uj = w + ((long(gl) * pc.nocc + j) * 2 + part) * pc.ld;
     T xf[nk] = {}, xg[nk] = {};
-    line_transform<T, N, KM, NT, NS>(psi + long(i) * pc.ld, uj, pc, t1, t2, rows, xf);
+    line_transform<T, N, KM, NT, NS>(psi + long(i) * pc.ld, uj, pc.cols, pc.ncol,
+                                      t1, t2, rows, xf);
     lds_barrier();
     if (i != j) {
-      line_transform<T, N, KM, NT, NS>(psi + long(j) * pc.ld, ui, pc, t1, t2, rows, xg);
+      line_transform<T, N, KM, NT, NS>(psi + long(j) * pc.ld, ui, pc.cols, pc.ncol,
+                                        t1, t2, rows, xg);
       lds_barrier();
     } else {
 #pragma unroll
@@ -370,6 +377,82 @@ __global__ __launch_bounds__(pair_threads(sizeof(T), N, KM),
   const long u = t - prefix[lo];
   const int gl = int(u / pc.npairs);
   pair_item<T, N, KM, false>(pc, gl, int(u - long(gl) * pc.npairs), reinterpret_cast<T*>(smem));
+}
+
+// Transforms of real fields to the half set H of auxiliary vectors, with the
+// same line transforms:
+//   OVERLAP = false, first pass of the double transform of chi: item r,
+//     out[o * ld + r] = scale sum_r' chi(r, r') e^{+iG_o.r'}   (a = chi)
+//   OVERLAP = true, overlap densities (step (i)): item (a, j),
+//     out[(a nh + o) nocc + j] = scale sum_r psi_a(r) psi_j(r) e^{-iG_o.r}
+//     (a = all orbitals, the nocc occupied ones first)
+// The fields come in the order r = (x N + z) N + y: the first transform runs
+// along x (consecutive lanes read consecutive (z, y)), the last along z; the
+// kept set is the same in every order of the axes.  The trigonometric
+// coefficients of all columns then meet in shared memory, where each output
+// combines its (up to) eight:
+//   sum f e^{i s G.r} = prod over axes of (C - i s sgn(k) S),  S = -sum f sin.
+// Bound by the line transforms and by reading the rows of chi; consecutive
+// items run on one XCD, so the 8-byte outputs of neighbouring rows fill
+// lines in its L2.  Against complex transforms of two rows (four products) per
+// workgroup, dispatched round-robin: rows of chi on the 36 grid 4136 -> 2169 us
+// (8.7 GB read), 24 grid 243 -> 180, 15 grid 35 -> 15, 18 grid FP64 129 -> 69;
+// overlap densities on the 36 grid 55 -> 15.5 ms.
+template <class T, int N, int KM, bool OVERLAP>
+__global__ __launch_bounds__(pair_threads(sizeof(T), N, KM), pair_minw(sizeof(T), N))
+void k_real_forward(const T* __restrict__ a, long ld, int nocc, long items,
+                    const int* __restrict__ cols, int ncol, const int* __restrict__ gdesc, int nh,
+                    int kmax, double scale, cplx<T>* __restrict__ out) {
+  constexpr int NT = pair_threads(sizeof(T), N, KM), NS = pair_slabs(sizeof(T), N, KM);
+  constexpr int nk = 2 * KM + 1, SP = N / NS;
+  extern __shared__ __align__(16) char smem[];
+  __shared__ int rows[nk];
+  const long per_xcd = (items + 7) / 8;
+  const long it = long(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+  if (it >= items) return;
+  T* t1 = reinterpret_cast<T*>(smem);
+  T* t2 = t1 + SP * nk * line_row(N);
+  const int tid = threadIdx.x;
+  row_table<nk, NT>(cols, ncol, rows);
+  T x[nk] = {};
+  long o0, step;
+  if constexpr (OVERLAP) {
+    const long av = it / nocc, j = it - av * nocc;
+    line_transform<T, N, KM, NT, NS>(a + (nocc + av) * ld, a + j * ld, cols, ncol, t1, t2, rows,
+                                     x);
+    o0 = av * nh * nocc + j;
+    step = nocc;
+  } else {
+    line_transform<T, N, KM, NT, NS, false>(a + it * ld, a + it * ld, cols, ncol, t1, t2, rows, x);
+    o0 = it;
+    step = ld;
+  }
+  __syncthreads();
+  if (tid < ncol)
+#pragma unroll
+    for (int k = 0; k < nk; ++k) t1[k * ncol + tid] = x[k];
+  __syncthreads();
+  for (int o = tid; o < nh; o += NT) {
+    const int g = gdesc[o];
+    int kx = g & 0xff, ky = ((g >> 8) & 0xff) - kmax, kz = (g >> 16) - kmax;
+    if (kx > N / 2) kx -= N;
+    const int ax = kx < 0 ? -kx : kx, ay = ky < 0 ? -ky : ky, az = kz < 0 ? -kz : kz;
+    // cosine rows and, where the index is not 0, sine rows one further
+    const T* c0 = t1 + (az ? 2 * az - 1 : 0) * ncol + (rows[ax ? 2 * ax - 1 : 0] & 0xffff) +
+                  (ay ? 2 * ay - 1 : 0);
+    const int dz = ncol;  // to the sine row of z, x and y
+    const int dx = ax ? (rows[2 * ax] & 0xffff) - (rows[2 * ax - 1] & 0xffff) : 0;
+    T re = c0[0], im = T(0);
+    const T sx = kx > 0 ? T(1) : T(-1), sy = ky > 0 ? T(1) : T(-1), sz = kz > 0 ? T(1) : T(-1);
+    if (ax) im -= sx * c0[dx];
+    if (ay) im -= sy * c0[1];
+    if (az) im -= sz * c0[dz];
+    if (ax && ay) re -= sx * sy * c0[dx + 1];
+    if (ax && az) re -= sx * sz * c0[dx + dz];
+    if (ay && az) re -= sy * sz * c0[1 + dz];
+    if (ax && ay && az) im += sx * sy * sz * c0[dx + 1 + dz];
+    out[o0 + o * step] = {T(scale) * re, OVERLAP ? -T(scale) * im : T(scale) * im};
+  }
 }
 
 // Occupied orbitals into the plane order of the pair transforms:

@@ -305,8 +305,9 @@ ltmp2_status prepare_cell(ltmp2_ctx* c, const cplx<double>* d_coef) {
   if ((s = ops->orbitals(d_coef, c->nst, c->npw, c->sc, 1.0 / std::sqrt(c->omega),
                          static_cast<T*>(c->d_psi), c->nrp, c->stream)))
     return fail(nullptr, s, "orbital synthesis launch failed");
-  if ((s = ops->overlap(static_cast<const T*>(c->d_psi), c->nrp, c->no, c->nv, c->d_gdesc, c->nh,
-                        c->kmax_aux, c->dV, static_cast<cplx<T>*>(c->d_nd), c->stream)))
+  if ((s = ops->overlap(static_cast<const T*>(c->d_psi), c->nrp, c->no, c->nv, c->d_cols, c->ncol,
+                        c->d_gdesc, c->nh, c->kmax_aux, c->dV, static_cast<cplx<T>*>(c->d_nd),
+                        c->stream)))
     return fail(nullptr, s, "overlap-density launch failed");
   // (the stream orders this after the orbital synthesis's reads of d_coef)
   if ((s = ops->plane_order(static_cast<const T*>(c->d_psi), c->nrp, c->no,
@@ -747,8 +748,9 @@ ltmp2_status run_direct_t(ltmp2_ctx* c, int itau, double* chi_out) {
   if (s) return fail(c, s, "chi tile launch failed");
   {
     StageTimer tm(c, 1);
-    s = ops->chi_rows(static_cast<const T*>(c->d_chi), c->nrp, c->nr, c->d_gdesc, c->nh,
-                      c->kmax_aux, c->dV, static_cast<cplx<T>*>(c->d_chihat), c->stream);
+    s = ops->chi_rows(static_cast<const T*>(c->d_chi), c->nrp, c->nr, c->d_cols, c->ncol,
+                      c->d_gdesc, c->nh, c->kmax_aux, c->dV, static_cast<cplx<T>*>(c->d_chihat),
+                      c->stream);
   }
   if (s) return fail(c, s, "chi row transform launch failed");
   {
