@@ -61,6 +61,7 @@ struct ltmp2_batch {
   bool failed = false;
   std::vector<void*> owned;
   size_t bytes = 0;
+  SideStream side;
   void *chi = nullptr, *chihat = nullptr, *P = nullptr, *wpool = nullptr;
   std::vector<Group> groups;
   hipGraph_t graph = nullptr;
@@ -138,14 +139,15 @@ void collect_batch_timing(ltmp2_batch* b) {
   b->marks.clear();
 }
 
-// the whole evaluation of one group (enqueued on the batch stream)
-ltmp2_status run_group(ltmp2_batch* b, const Group& g) {
+// the whole evaluation of one group (direct terms on `side`, the rest on the
+// batch stream)
+ltmp2_status run_group(ltmp2_batch* b, const Group& g, hipStream_t side) {
   ltmp2_status s;
   for (int it = 0; it < g.max_ntau; ++it) {
     for (int ci : g.cells) {
       ltmp2_ctx* c = b->cells[ci];
       if (it >= c->ntau) continue;
-      if ((s = run_direct(c, it, nullptr))) return bfail(b, s, "cell direct term: " + c->err);
+      if ((s = run_direct(c, it, side))) return bfail(b, s, "cell direct term: " + c->err);
     }
     for (int r = 0; r < g.rounds; ++r) {
       for (int ci : g.cells) {
@@ -170,8 +172,9 @@ ltmp2_status run_group(ltmp2_batch* b, const Group& g) {
 }
 
 ltmp2_status run_all(ltmp2_batch* b) {
+  Beside beside(b->side, b->stream, !b->timing);
   for (const Group& g : b->groups) {
-    ltmp2_status s = run_group(b, g);
+    ltmp2_status s = run_group(b, g, beside.stream());
     if (s) return s;
   }
   return LTMP2_OK;
@@ -212,6 +215,7 @@ extern "C" ltmp2_status ltmp2_batch_create(int n_cells, const ltmp2_params* para
     }
     b->own_stream = true;
   }
+  b->side.create();
   b->prec = prec;
   // per-cell preparation without private scratch
   for (int k = 0; k < n_cells; ++k) {
@@ -456,6 +460,7 @@ extern "C" void ltmp2_batch_destroy(ltmp2_batch* b) {
   if (b->graph) (void)hipGraphDestroy(b->graph);
   for (ltmp2_ctx* c : b->cells) ltmp2_destroy(c);
   for (void* p : b->owned) (void)hipFree(p);
+  b->side.destroy();
   if (b->own_stream) (void)hipStreamDestroy(b->stream);
   delete b;
 }

@@ -675,6 +675,7 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
   }
   // transformed-state buffers last, sized by what the cap leaves
   if (c->own_scratch) {
+    c->side.create();
     if (P.workspace_cap) {
       if (c->bytes + per_g > P.workspace_cap)
         return fail(nullptr, LTMP2_ENOMEM, "device footprint exceeds the workspace cap");
@@ -981,8 +982,15 @@ PairCell pair_cell(const ltmp2_ctx* c, int g0, int gb) {
                   c->d_xpart + size_t(g0) * c->npairs, c->nrp, c->no, c->npairs, gb,
                   c->kmax_aux, c->ncol, c->nm2, c->dV * c->dV};
 }
-ltmp2_status run_direct(ltmp2_ctx* c, int itau, double* chi_out) {
-  return direct_tau(c, itau, chi_out);
+// the direct term on a stream other than the context's
+ltmp2_status run_direct(ltmp2_ctx* c, int itau, hipStream_t st) {
+  const hipStream_t own = c->stream;
+  c->stream = st;
+  if (c->beta) c->beta->stream = st;
+  const ltmp2_status s = direct_tau(c, itau, nullptr);
+  c->stream = own;
+  if (c->beta) c->beta->stream = own;
+  return s;
 }
 ltmp2_status run_exchange(ltmp2_ctx* c, int itau, int g_first, int g_count) {
   return exchange_tau(c, itau, g_first, g_count);
@@ -1283,11 +1291,15 @@ extern "C" ltmp2_status ltmp2_energy(ltmp2_ctx* c, double* e_direct, double* e_e
                                      double* per_tau, double* quad_err) {
   ltmp2_status s = usable(c, 0);
   if (s) return s;
-  for (int t = 0; t < c->ntau; ++t) {
-    if ((s = direct_tau(c, t, nullptr))) return s;
-    if ((s = exchange_tau(c, t, 0, c->nh))) return s;
-    if (c->beta && (s = exchange_tau(c->beta, t, 0, c->nh)))
-      return fail(c, s, "spin beta: " + c->beta->err);
+  {
+    // stage times are taken on one stream
+    Beside beside(c->side, c->stream, !c->timing);
+    for (int t = 0; t < c->ntau; ++t) {
+      if ((s = run_direct(c, t, beside.stream()))) return s;
+      if ((s = exchange_tau(c, t, 0, c->nh))) return s;
+      if (c->beta && (s = exchange_tau(c->beta, t, 0, c->nh)))
+        return fail(c, s, "spin beta: " + c->beta->err);
+    }
   }
   std::vector<double> pt(2 * size_t(c->ntau)), pb;
   HIPCHK(c, hipMemcpyAsync(pt.data(), c->d_scal, sizeof(double) * pt.size(), hipMemcpyDeviceToHost,
@@ -1392,6 +1404,7 @@ extern "C" void ltmp2_destroy(ltmp2_ctx* c) {
   if (c->stream || !c->owned.empty()) (void)hipStreamSynchronize(c->stream);
   collect_timing(c);
   for (hipEvent_t e : c->pool) (void)hipEventDestroy(e);
+  c->side.destroy();
   for (void* p : c->owned) (void)hipFree(p);
   delete c;
 }
