@@ -92,11 +92,9 @@ ltmp2_status launch_split3(const float* src, long lds, int K, int Kpad, int M, l
                            const double* sk, int mode, void* hi, void* lo, long o0,
                            hipStream_t st) {
   if (Kpad % 64 != 0 || K > Kpad || M > ldo) return LTMP2_EINVAL;
-  const long items = long(Kpad / 8) * M;
-  if (items == 0) return LTMP2_OK;
-  hipLaunchKernelGGL(k_split3, dim3(unsigned((items + 255) / 256)), dim3(256), 0, st, src, lds, K,
-                     Kpad, M, ldo, sk, mode, static_cast<__bf16*>(hi), static_cast<__bf16*>(lo),
-                     o0);
+  if (Kpad <= 0 || M <= 0 || K <= 0) return LTMP2_OK;
+  hipLaunchKernelGGL(k_split3, dim3((M + 255) / 256, Kpad / 8), dim3(256), 0, st, src, lds, K, M,
+                     ldo, sk, mode, static_cast<__bf16*>(hi), static_cast<__bf16*>(lo), o0);
   return hipGetLastError() == hipSuccess ? LTMP2_OK : LTMP2_EDEVICE;
 }
 
