@@ -92,15 +92,13 @@ struct ltmp2_ctx {
   int* d_cdesc = nullptr;
   int* d_cstart = nullptr;
   int* d_ckx = nullptr;
-  int* d_wq = nullptr;
-  signed char* d_wsgn = nullptr;
-  int* d_wx = nullptr;
+  void* d_wtab = nullptr;         // coefficients of the transformed states (GridOps::wstates)
   int* d_gdesc = nullptr;
   int* d_pairs = nullptr;
   int* d_cols = nullptr;          // [ncol] columns of the pair transforms (PairCell)
-  double* d_vm2 = nullptr;        // [nm2] v(G) by m^2
   signed char* d_shm2 = nullptr;  // [nm2] spheres by m^2 (cutoff extrapolation)
-  int ncol = 0, nm2 = 0;
+  int ncol = 0, nm2 = 0, m2lim = 0;  // PairCell
+  double vden = 0.0;
   double* d_v = nullptr;
   double* d_fo = nullptr;  // [ntau][no]
   double* d_fv = nullptr;  // [ntau][nv]
@@ -109,6 +107,7 @@ struct ltmp2_ctx {
   size_t esz = sizeof(double);
   void* d_psi = nullptr;       // [nst][nrp]
   void* d_psiz = nullptr;      // [no][nrp] occupied, in the plane order of the pair transforms
+                               // (null: see occupied())
   void* d_nd = nullptr;        // [nv][nh][no] complex
   void* d_bpw = nullptr;       // [nv][ldbpw] real basis of virtual coefficients
   void* d_chi = nullptr;       // [nrp][nrp]
@@ -158,6 +157,8 @@ ltmp2_status run_direct(ltmp2_ctx* c, int itau, hipStream_t st);
 ltmp2_status run_exchange(ltmp2_ctx* c, int itau, int g_first, int g_count);
 // Pieces of run_exchange used by batched execution.
 PairCell pair_cell(const ltmp2_ctx* c, int g0, int gb);
+// Occupied orbitals in the pair transforms' order: kept, or in the chi scratch.
+inline void* occupied(const ltmp2_ctx* c) { return c->d_psiz ? c->d_psiz : c->d_chihat; }
 ltmp2_status exchange_block_prepare(ltmp2_ctx* c, int itau, int g0, int gb);
 ltmp2_status exchange_reduce(ltmp2_ctx* c, int itau, int g_first, int g_count);
 ltmp2_status setup_cell(ltmp2_ctx* c, const int32_t* miller, const double* eps,

@@ -33,10 +33,10 @@ struct GridOps {
   ltmp2_status (*chi_cols)(const cplx<T>* chihat, long ld, const int* gdesc, int ng, int nh,
                            const double* v, int kmax, double dV, double* pd,
                            cplx<double>* chi_out, ShellBins bins, hipStream_t st);
-  // wx: index table of the window wstates_window(n, sc.kmax) (null if none)
-  ltmp2_status (*wstates)(const T* P, int npw, const int* wq, const signed char* wsgn,
-                          const int* wx, SphereCols sc, int nitems, double scale, T* w, long ld,
-                          hipStream_t st);
+  // tab: wx of kernels_wstates.hpp for the window wstates_kept(sc.kmax, npw), wq
+  // of k_wstates where that is -1
+  ltmp2_status (*wstates)(const T* P, int npw, const void* tab, SphereCols sc, int nitems,
+                          double scale, T* w, long ld, hipStream_t st);
   // pair transforms of one block of outer vectors of a cell
   ltmp2_status (*pair)(const PairCell& pc, hipStream_t st);
   // the same for several cells of one kept-set instance (device arrays
@@ -52,6 +52,8 @@ struct GridOps {
   ltmp2_status (*plane_order)(const T* in, long ld, int nocc, T* out, hipStream_t st);
   // kept-set instance of the pair kernels for a cell's kmax (-1: none)
   int (*pair_kept)(int kmax);
+  // window instance of the transformed states for a cell (-1: general kernel)
+  int (*wstates_kept)(int kmax, int npw);
 };
 
 template <class T>

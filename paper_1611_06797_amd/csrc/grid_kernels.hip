@@ -122,25 +122,30 @@ ltmp2_status hartree(const cplx<T>* h, long ld, const int* gdesc, int ng, const 
 }
 
 template <class T, int K>
-ltmp2_status wstates_window_launch(const T* P, int npw, const int* wx, int nitems, double scale,
+ltmp2_status wstates_window_launch(const T* P, int npw, const void* tab, int nitems, double scale,
                                    T* w, long ld, hipStream_t st) {
   using W = WstShape<T, N, K>;
   return launch_nt(k_wstates_real<T, N, K>, dim3(unsigned(2L * nitems / W::F)), W::NT, W::lds(npw),
-                   st, P, npw, wx, scale, w, ld);
+                   st, P, npw, static_cast<const unsigned short*>(tab), scale, w, ld);
+}
+
+// Window instance of the transformed states for a cell (-1: the general kernel,
+// also for a set so far from a sphere that it leaves no room next to the field)
+template <class T>
+int wstates_kept(int kmax, int npw) {
+  constexpr int ko = korb_win(N), kl = ko < 2 ? ko : ko - 1;
+  const int win = wstates_window(N, kmax);
+  const size_t lds = win == ko ? WstShape<T, N, ko>::lds(npw) : WstShape<T, N, kl>::lds(npw);
+  return lds <= kLdsCap ? win : -1;
 }
 
 template <class T>
-ltmp2_status wstates(const T* P, int npw, const int* wq, const signed char* wsgn, const int* wx,
-                     SphereCols sc, int nitems, double scale, T* w, long ld, hipStream_t st) {
+ltmp2_status wstates(const T* P, int npw, const void* tab, SphereCols sc, int nitems, double scale,
+                     T* w, long ld, hipStream_t st) {
   constexpr int ko = korb_win(N), kl = ko < 2 ? ko : ko - 1;
-  // (a set far from a sphere can be too large for shared memory next to the field)
-  if (wx) {
-    const int win = wstates_window(N, sc.kmax);
-    if (win == ko && WstShape<T, N, ko>::lds(npw) <= kLdsCap)
-      return wstates_window_launch<T, ko>(P, npw, wx, nitems, scale, w, ld, st);
-    if (win == kl && WstShape<T, N, kl>::lds(npw) <= kLdsCap)
-      return wstates_window_launch<T, kl>(P, npw, wx, nitems, scale, w, ld, st);
-  }
+  const int win = wstates_kept<T>(sc.kmax, npw);
+  if (win == ko) return wstates_window_launch<T, ko>(P, npw, tab, nitems, scale, w, ld, st);
+  if (win == kl) return wstates_window_launch<T, kl>(P, npw, tab, nitems, scale, w, ld, st);
   // the largest slab tile that lets four workgroups share a CU, unless two
   // workgroups per CU would allow more than twice that tile
   const int nk = 2 * sc.kmax + 1;
@@ -151,8 +156,8 @@ ltmp2_status wstates(const T* P, int npw, const int* wq, const signed char* wsgn
   };
   const int s4 = tile(kLdsQuarter), s2 = tile(kLdsHalf);
   const int sx = 2 * s4 >= s2 ? s4 : s2;
-  return launch(k_wstates<T, N>, dim3(nitems), inv_lds_bytes<T>(N, nk, sx), st, P, npw, wq, wsgn,
-                sc, sx, scale, w, ld);
+  return launch(k_wstates<T, N>, dim3(nitems), inv_lds_bytes<T>(N, nk, sx), st, P, npw,
+                static_cast<const int*>(tab), sc, sx, scale, w, ld);
 }
 
 // Kept-set instance of the pair kernels for a cell (-1: none holds it).
@@ -269,8 +274,9 @@ ltmp2_status plane_order(const T* in, long ld, int nocc, T* out, hipStream_t st)
   template ltmp2_status chi_cols<T>(const cplx<T>*, long, const int*, int, int, const double*, \
                                     int, double, double*, cplx<double>*, ShellBins,            \
                                     hipStream_t);                                              \
-  template ltmp2_status wstates<T>(const T*, int, const int*, const signed char*, const int*,  \
-                                   SphereCols, int, double, T*, long, hipStream_t);            \
+  template ltmp2_status wstates<T>(const T*, int, const void*, SphereCols, int, double, T*, long,\
+                                   hipStream_t);                                               \
+  template int wstates_kept<T>(int, int);                                                      \
   template ltmp2_status pair<T>(const PairCell&, hipStream_t);                                 \
   template ltmp2_status pair_multi<T>(const PairCell*, const long*, int, long, int, int,       \
                                       hipStream_t);                                            \
@@ -291,11 +297,11 @@ extern const GridOps<float> LTMP2_CAT(kGridOpsF_, LTMP2_N);
 const GridOps<double> LTMP2_CAT(kGridOpsD_, LTMP2_N) = {
     orbitals<double>, overlap<double>, chi_rows<double>, chi_cols<double>, wstates<double>,
     pair<double>, pair_multi<double>, hartree<double>, pair_shape<double>, plane_order<double>,
-    pair_instance};
+    pair_instance, wstates_kept<double>};
 const GridOps<float> LTMP2_CAT(kGridOpsF_, LTMP2_N) = {
     orbitals<float>, overlap<float>, chi_rows<float>, chi_cols<float>, wstates<float>,
     pair<float>, pair_multi<float>, hartree<float>, pair_shape<float>, plane_order<float>,
-    pair_instance};
+    pair_instance, wstates_kept<float>};
 #endif
 
 }  // namespace ltmp2

@@ -163,13 +163,13 @@ __global__ __launch_bounds__(kThreads) void k_hartree(const cplx<T>* __restrict_
 // of kernels_wstates.hpp (the caller's grid aliases; see there for P and w):
 // both fields as one complex transform, W_j(G) gathered from P where the x
 // stage needs it.
-// Entry e of the sphere (column order) uses wq[e] = q_re | (q_im + 1) << 16
-// and the sign s = +1 for G_k, -1 for -G_k (c_a(-G) = conj c_a(G)):
-//   W(G) = (P_re[q_re] - s P_im[q_im]) + i (P_im[q_re] + s P_re[q_im]).
+// Entry e of the sphere (column order) uses wq[e] = q, the place of Re c(G_k) in
+// a row of P (Im c(G_k) follows it; 0 for G = 0, which has none), bit 31 set for
+// -G_k.  With s = +1 for G_k and -1 for -G_k (c_a(-G) = conj c_a(G)):
+//   W(G) = (P_re[q] - s P_im[q + 1]) + i (P_im[q] + s P_re[q + 1]).
 template <class T, int N>
 __global__ __launch_bounds__(kThreads) void k_wstates(const T* __restrict__ P, int npw,
                                                       const int* __restrict__ wq,
-                                                      const signed char* __restrict__ wsgn,
                                                       SphereCols sc, int sx, double scale,
                                                       T* __restrict__ w, long ld) {
   extern __shared__ __align__(16) char smem[];
@@ -183,13 +183,12 @@ __global__ __launch_bounds__(kThreads) void k_wstates(const T* __restrict__ P, i
   // W_j(G) of sphere entry e, gathered from the real basis (each entry is
   // used once per slab group)
   auto cf = [&](int, int e) {
-    const int q = wq[e];
-    const int qr = q & 0xffff, qi = (q >> 16) - 1;
-    const T s = T(wsgn[e]);
-    T re = pre[qr], im = pim[qr];
-    if (qi >= 0) {
-      re -= s * pim[qi];
-      im += s * pre[qi];
+    const int q = wq[e] & 0xffff;
+    T re = pre[q], im = pim[q];
+    if (q > 0) {
+      const T s = wq[e] < 0 ? T(-1) : T(1);
+      re -= s * pim[q + 1];
+      im += s * pre[q + 1];
     }
     return cplx<T>{re, im};
   };

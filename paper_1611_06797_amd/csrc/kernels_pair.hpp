@@ -47,11 +47,11 @@ struct PairCell {
   const void* w;       // [gb][nocc][2][ld] real and imaginary parts of w (T)
   const int* pairs;    // [npairs] i | j << 16
   const int* cols;     // [ncol] kept (ky, kz) columns: row index ry | rz << 8
-  const double* vm2;   // [nm2] v(G) by m^2 = (|G| / b)^2, 0 outside the set
   double* xpart;       // [gb][npairs] partial sums of this block
   long ld;
-  int nocc, npairs, gb, kmax, ncol, nm2;
-  double dV2;
+  // v(G) by m^2 = (|G| / b)^2 < nm2: 4 pi / (vden m^2) up to m2lim, else 0
+  int nocc, npairs, gb, kmax, ncol, nm2, m2lim;
+  double dV2, vden;
   // optional split by auxiliary cutoff shell (ShellBins): number of spheres
   // by m^2 (1 outside the set, where v = 0), the shells of the outer vectors
   // from the block's first one on, and xbins [gb][npairs][nb]
@@ -282,7 +282,7 @@ __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* 
   // tables by m^2 in shared memory: read one column at a time in the
   // epilogue, a chain of dependent global reads otherwise (36 grid 115 -> 94)
   for (int k = tid; k < pc.nm2; k += NT) {
-    vm[k] = pc.vm2[k];
+    vm[k] = k >= 1 && k <= pc.m2lim ? 4.0 * M_PI / (pc.vden * double(k)) : 0.0;
     if constexpr (BINS)
       if (split) sh[k] = pc.shm2[k];
   }

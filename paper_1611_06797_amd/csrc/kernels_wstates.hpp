@@ -58,12 +58,13 @@ struct WstShape {
 };
 
 // wx [2 K + 1][(K + 1)(2 K + 1)]: for kx and slot (kz, ky), the index of the
-// coefficient pair in a row of P (0: G = 0; (npw + 1) / 2: none), bit 31 set
-// where its conjugate is meant.
+// coefficient pair in a row of P (0: G = 0; (npw + 1) / 2: none), bit 15 set
+// where its conjugate is meant (sets that fit shared memory have fewer than 2^15
+// pairs).
 template <class T, int N, int K>
 __global__ __launch_bounds__((WstShape<T, N, K>::NT), (WstShape<T, N, K>::MINW))
-void k_wstates_real(const T* __restrict__ P, int npw, const int* __restrict__ wx, double scale,
-                    T* __restrict__ w, long ld) {
+void k_wstates_real(const T* __restrict__ P, int npw, const unsigned short* __restrict__ wx,
+                    double scale, T* __restrict__ w, long ld) {
   using W = WstShape<T, N, K>;
   constexpr int F = W::F, SP = W::SP, R = W::R, NT = W::NT, nk = W::nk;
   extern __shared__ __align__(16) char smem[];
@@ -104,8 +105,8 @@ void k_wstates_real(const T* __restrict__ P, int npw, const int* __restrict__ wx
         v[x] = {T(0), T(0)};
         if (kx >= -K && kx <= K) {
           const int code = wx[(kx + K) * W::NSLOT + sl];
-          v[x] = co[f * nce + (code & 0x7fffffff)];
-          v[x].y = code < 0 ? -v[x].y : v[x].y;
+          v[x] = co[f * nce + (code & 0x7fff)];
+          v[x].y = code & 0x8000 ? -v[x].y : v[x].y;
         }
       }
       Fft<T, 1, N>::run(v);

@@ -310,7 +310,7 @@ ltmp2_status prepare_cell(ltmp2_ctx* c, const cplx<double>* d_coef) {
                         c->stream)))
     return fail(nullptr, s, "overlap-density launch failed");
   // (the stream orders this after the orbital synthesis's reads of d_coef)
-  if ((s = ops->plane_order(static_cast<const T*>(c->d_psi), c->nrp, c->no,
+  if (c->d_psiz && (s = ops->plane_order(static_cast<const T*>(c->d_psi), c->nrp, c->no,
                             static_cast<T*>(c->d_psiz), c->stream)))
     return fail(nullptr, s, "orbital reordering launch failed");
   return LTMP2_OK;
@@ -426,9 +426,8 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
       if (row_k(ry) * row_k(ry) + row_k(rz) * row_k(rz) <= lim) cols.push_back(ry | (rz << 8));
   c->ncol = (int)cols.size();
   c->nm2 = 2 * km_pair * km_pair + 2 * km_pair + 1;
-  std::vector<double> vm2(c->nm2, 0.0);
-  for (int m2 = 1; m2 < c->nm2 && m2 <= lim; ++m2)
-    vm2[m2] = 4.0 * M_PI / (c->omega * b * b * double(m2));
+  c->m2lim = lim;
+  c->vden = c->omega * b * b;
   if (c->nb) {
     shm2.assign(c->nm2, 1);
     for (int m2 = 1; m2 < c->nm2 && m2 <= lim; ++m2) {
@@ -476,37 +475,30 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
   }
   if (zero_idx < 0 || nq != c->npw)
     return fail(nullptr, LTMP2_EINVAL, "basis must contain G = 0 and be symmetric");
-  std::vector<int> wq(c->npw);
-  std::vector<signed char> wsgn(c->npw);
+  // table of the transformed states (GridOps::wstates): by (kx, kz >= 0, ky) for
+  // the kernels of a sphere window, else by sphere entry
+  const int kw = P.prec == LTMP2_FP64 ? grid_ops<double>(n)->wstates_kept(ko, c->npw)
+                                      : grid_ops<float>(n)->wstates_kept(ko, c->npw);
+  const int nkw = 2 * kw + 1, slots = (kw + 1) * nkw;
+  std::vector<int> wq(kw < 0 ? size_t(c->npw) : 0);
+  std::vector<unsigned short> wx(kw < 0 ? 0 : size_t(nkw) * slots,
+                                 static_cast<unsigned short>((c->npw + 1) / 2));
   for (int e = 0; e < c->npw; ++e) {
     const int i = order[e];
     const int x = miller[3 * i], y = miller[3 * i + 1], z = miller[3 * i + 2];
-    if (x == 0 && y == 0 && z == 0) {
-      wq[e] = 0;
-      wsgn[e] = 1;
-    } else if (positive_half(x, y, z)) {
-      const int q = qre[std::make_tuple(x, y, z)];
-      wq[e] = q | ((q + 1 + 1) << 16);
-      wsgn[e] = 1;
-    } else {
-      const int q = qre[std::make_tuple(-x, -y, -z)];
-      wq[e] = q | ((q + 1 + 1) << 16);
-      wsgn[e] = -1;
+    int q = 0;
+    bool neg = false;
+    if (positive_half(x, y, z)) {
+      q = qre[std::make_tuple(x, y, z)];
+    } else if (x != 0 || y != 0 || z != 0) {
+      q = qre[std::make_tuple(-x, -y, -z)];
+      neg = true;
     }
-  }
-  // the same by (kx, kz >= 0, ky) for the kernels of a sphere window
-  std::vector<int> wx;
-  const int kwx = wstates_window(c->n, ko);
-  if (kwx >= 0) {
-    const int nkw = 2 * kwx + 1, slots = (kwx + 1) * nkw;
-    wx.assign(size_t(nkw) * slots, (c->npw + 1) / 2);
-    for (int e = 0; e < c->npw; ++e) {
-      const int i = order[e], x = miller[3 * i], y = miller[3 * i + 1], z = miller[3 * i + 2];
-      if (z < 0) continue;
-      const int q = wq[e] & 0xffff, s = z * nkw + y + kwx;
-      wx[size_t(x + kwx) * slots + s] =
-          ((q + 1) / 2) | int(wsgn[e] < 0 ? 0x80000000u : 0u);
-    }
+    if (kw < 0)
+      wq[e] = int(unsigned(q) | (neg ? 0x80000000u : 0u));
+    else if (z >= 0)
+      wx[size_t(x + kw) * slots + z * nkw + y + kw] =
+          static_cast<unsigned short>((q + 1) / 2 | (neg ? 0x8000 : 0));
   }
   // coefficients in column order, and the real basis of the virtual ones
   std::vector<double> coef_col(2 * size_t(c->nst) * c->npw);
@@ -615,14 +607,16 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
     return fail(nullptr, LTMP2_EINVAL, "orbital sphere above 65535 plane waves");
   // device allocations and uploads
   ltmp2_status s;
+  int* d_wq = nullptr;
+  unsigned short* d_wx = nullptr;
   if ((s = upload(c, &c->d_cdesc, cdesc)) || (s = upload(c, &c->d_cstart, cstart)) ||
-      (s = upload(c, &c->d_ckx, ckx)) || (s = upload(c, &c->d_wq, wq)) ||
-      (s = upload(c, &c->d_wsgn, wsgn)) ||
-      (!wx.empty() && (s = upload(c, &c->d_wx, wx))) || (s = upload(c, &c->d_gdesc, gdesc)) ||
+      (s = upload(c, &c->d_ckx, ckx)) || (s = kw < 0 ? upload(c, &d_wq, wq) : upload(c, &d_wx, wx)) ||
+      (s = upload(c, &c->d_gdesc, gdesc)) ||
       (s = upload(c, &c->d_pairs, pairs)) || (s = upload(c, &c->d_cols, cols)) ||
-      (s = upload(c, &c->d_vm2, vm2)) || (s = upload(c, &c->d_v, v)) ||
+      (s = upload(c, &c->d_v, v)) ||
       (s = upload(c, &c->d_fo, fo)) || (s = upload(c, &c->d_fv, fv)))
     return s;
+  c->d_wtab = kw < 0 ? static_cast<void*>(d_wq) : d_wx;
   if (es == sizeof(double)) {
     double* d = nullptr;
     if ((s = upload(c, &d, bpw))) return s;
@@ -636,12 +630,17 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
   c->sc = SphereCols{(int)cdesc.size(), ko, c->d_cdesc, c->d_cstart, c->d_ckx};
   // the coefficients are needed until the orbitals are on the grid; their
   // memory then holds the occupied orbitals in the pair transforms' order
-  const size_t psiz_bytes = es * size_t(c->no) * nrp;
+  // (with few coefficients the buffer grows to hold them, but not under a
+  // workspace cap, where they go through the chi scratch, see order_occupied)
+  const size_t psiz_len = (es * size_t(c->no) * nrp + sizeof(double) - 1) / sizeof(double);
+  const bool keep_psiz =
+      psiz_len <= coef_col.size() || !P.workspace_cap || c->no > 2 * c->nh;
   double* d_coef = nullptr;
-  if ((s = dalloc(c, &d_coef, std::max(coef_col.size(), psiz_bytes / sizeof(double) + 1)))) return s;
+  if ((s = dalloc(c, &d_coef, keep_psiz ? std::max(coef_col.size(), psiz_len) : coef_col.size())))
+    return s;
   HIPCHK(c, hipMemcpy(d_coef, coef_col.data(), coef_col.size() * sizeof(double),
                       hipMemcpyHostToDevice));
-  c->d_psiz = d_coef;
+  c->d_psiz = keep_psiz ? d_coef : nullptr;
   if ((s = dalloc_bytes(c, &c->d_psi, es * size_t(c->nst) * nrp)) ||
       (s = dalloc_bytes(c, &c->d_nd, es * 2 * size_t(c->nv) * c->nh * c->no)) ||
       (c->own_scratch && (s = dalloc_bytes(c, &c->d_chi, es * nrp * nrp))) ||
@@ -809,8 +808,8 @@ ltmp2_status block_prepare_t(ltmp2_ctx* c, int itau, int g0, int gb) {
   if (s) return fail(c, s, "transformed-state GEMM launch failed");
   {
     StageTimer tm(c, 4);
-    s = ops->wstates(static_cast<const T*>(c->d_P), c->npw, c->d_wq, c->d_wsgn, c->d_wx, c->sc,
-                     gb * c->no, 1.0 / std::sqrt(c->omega), static_cast<T*>(c->d_w), c->nrp,
+    s = ops->wstates(static_cast<const T*>(c->d_P), c->npw, c->d_wtab, c->sc, gb * c->no,
+                     1.0 / std::sqrt(c->omega), static_cast<T*>(c->d_w), c->nrp,
                      c->stream);
   }
   if (s) return fail(c, s, "transformed-state launch failed");
@@ -858,9 +857,24 @@ ltmp2_status block_prepare(ltmp2_ctx* c, int itau, int g0, int gb) {
   }
 }
 
+// A context that does not keep its occupied orbitals in the pair transforms'
+// order puts them into the chi scratch ahead of each use.
+template <class T>
+ltmp2_status order_occupied_t(ltmp2_ctx* c) {
+  if (c->d_psiz) return LTMP2_OK;
+  const ltmp2_status s =
+      grid_ops<T>(c->n)->plane_order(static_cast<const T*>(c->d_psi), c->nrp, c->no,
+                                     static_cast<T*>(occupied(c)), c->stream);
+  return s ? fail(c, s, "orbital reordering launch failed") : LTMP2_OK;
+}
+ltmp2_status order_occupied(ltmp2_ctx* c) {
+  return c->prm.prec == LTMP2_FP64 ? order_occupied_t<double>(c) : order_occupied_t<float>(c);
+}
+
 // exchange term at one Laplace point for G' in H[g_first, g_first + g_count)
 ltmp2_status exchange_tau(ltmp2_ctx* c, int itau, int g_first, int g_count) {
-  ltmp2_status s;
+  ltmp2_status s = order_occupied(c);
+  if (s) return s;
   for (int g0 = g_first; g0 < g_first + g_count; g0 += c->gblock) {
     const int gb = std::min(c->gblock, g_first + g_count - g0);
     if ((s = block_prepare(c, itau, g0, gb))) return s;
@@ -941,10 +955,11 @@ ltmp2_status hartree_tau_t(ltmp2_ctx* c, int itau) {
   const GridOps<T>* ops = grid_ops<T>(c->n);
   ltmp2_status s;
   cplx<T>* h = static_cast<cplx<T>*>(c->d_chi);  // free outside the chi route
+  if ((s = order_occupied_t<T>(c))) return s;
   for (int g0 = 0; g0 < c->nh; g0 += c->gblock) {
     const int gb = std::min(c->gblock, c->nh - g0);
     if ((s = block_prepare(c, itau, g0, gb))) return s;
-    if ((s = launch_hsum<T>(static_cast<const T*>(c->d_psiz), c->nrp,
+    if ((s = launch_hsum<T>(static_cast<const T*>(occupied(c)), c->nrp,
                             static_cast<const T*>(c->d_w), c->no, c->nr, gb, h, c->stream)))
       return fail(c, s, "state-sum launch failed");
     if ((s = ops->hartree(h, c->nrp, c->d_gdesc, c->ng, c->d_v, c->kmax_aux, c->dV, g0, gb,
@@ -978,9 +993,9 @@ extern "C" ltmp2_status ltmp2_direct_hartree(ltmp2_ctx* c, int itau, double* e_d
 
 namespace ltmp2 {
 PairCell pair_cell(const ltmp2_ctx* c, int g0, int gb) {
-  return PairCell{c->d_psiz, c->d_w,  c->d_pairs, c->d_cols,   c->d_vm2,
+  return PairCell{occupied(c), c->d_w, c->d_pairs, c->d_cols,
                   c->d_xpart + size_t(g0) * c->npairs, c->nrp, c->no, c->npairs, gb,
-                  c->kmax_aux, c->ncol, c->nm2, c->dV * c->dV};
+                  c->kmax_aux, c->ncol, c->nm2, c->m2lim, c->dV * c->dV, c->vden};
 }
 // the direct term on a stream other than the context's
 ltmp2_status run_direct(ltmp2_ctx* c, int itau, hipStream_t st) {
@@ -1292,8 +1307,10 @@ extern "C" ltmp2_status ltmp2_energy(ltmp2_ctx* c, double* e_direct, double* e_e
   ltmp2_status s = usable(c, 0);
   if (s) return s;
   {
-    // stage times are taken on one stream
-    Beside beside(c->side, c->stream, !c->timing);
+    // stage times are taken on one stream, and occupied orbitals in the chi
+    // scratch allow no direct term beside
+    const bool want = !c->timing && c->d_psiz && (!c->beta || c->beta->d_psiz);
+    Beside beside(c->side, c->stream, want);
     for (int t = 0; t < c->ntau; ++t) {
       if ((s = run_direct(c, t, beside.stream()))) return s;
       if ((s = exchange_tau(c, t, 0, c->nh))) return s;
