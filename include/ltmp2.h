@@ -424,11 +424,11 @@ const char* ltmp2_mlp_last_error(void);
 /*
  * Batched evaluation of many independent cells (grown form: many small cells
  * of uneven size, each with its own Laplace grid).  Cells are grouped by FFT
- * grid; per Laplace point and round of outer G', one persistent fused launch
- * evaluates the Fock-like pair transforms of every cell of a group; the large
- * scratch is pooled; a tuner picks the pair kernel's slab tile and resident
- * workgroups per CU on first use; the launch sequence is captured into a
- * hipGraph after the first (eager) evaluation and replayed afterwards.
+ * grid; per Laplace point and round of outer G', one fused launch evaluates the
+ * Fock-like pair transforms of every cell of a group, and the direct terms run
+ * on a second stream; the large scratch is pooled; the launch sequence is
+ * captured into a hipGraph after the first (eager) evaluation and replayed
+ * afterwards.
  * Per-cell arrays are as in ltmp2_setup; tau / w may be NULL (or hold NULL
  * entries for cells without a given quadrature).  All cells must use the same
  * precision.  If hip_stream is NULL the batch creates its own stream.
