@@ -122,10 +122,13 @@ __host__ __device__ constexpr int pair_threads(size_t es, int n, int k) {
 }
 
 // Waves per SIMD the launch bounds ask for: the register need is about three
-// line lengths (six in FP64).
-__host__ __device__ constexpr int pair_minw(size_t es, int n) {
-  if (es == 8) return n <= 12 ? 6 : n <= 18 ? 4 : n <= 24 ? 3 : 2;
-  return n <= 15 ? 8 : n <= 20 ? 6 : n <= 24 ? 5 : 4;
+// line lengths (six in FP64).  The split by cutoff shell adds its bins to the
+// epilogue: one wave fewer on the small grids, whose instances spill otherwise
+// (15 grid, |k| <= 7, FP32: 16.0 ns per item with eight, 14.2 with seven; 12
+// grid, |k| <= 5, FP64: 11.9 with six, 11.1 with five).
+__host__ __device__ constexpr int pair_minw(size_t es, int n, bool bins = false) {
+  if (es == 8) return n <= 12 ? (bins ? 5 : 6) : n <= 18 ? 4 : n <= 24 ? 3 : 2;
+  return n <= 15 ? (bins ? 7 : 8) : n <= 20 ? 6 : n <= 24 ? 5 : 4;
 }
 
 // Barrier that orders shared memory only: global loads stay in flight.
@@ -263,7 +266,10 @@ __device__ __forceinline__ void line_transform(const T* pa, const T* pu, const i
 }
 
 // One (G', pair) item.  BINS: the per-shell split of the cutoff extrapolation
-// is compiled in (taken when pc.shm2 is set).
+// is compiled in (taken when pc.shm2 is set).  A thread's eight bins live in
+// registers for the epilogue of one part only; kept across the transforms of
+// both parts they spilled (15 grid, |k| <= 7, FP32: 23.7 ns per item against
+// 14.2; 20 grid, |k| <= 9: 41.8 and 32.3; 12 grid, |k| <= 3, FP64: 12.3 and 9.0).
 template <class T, int N, int KM, bool BINS>
 __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* t1) {
   constexpr int NT = pair_threads(sizeof(T), N, KM), NS = pair_slabs(sizeof(T), N, KM);
@@ -272,7 +278,8 @@ __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* 
   __shared__ double vm[kM2];
   __shared__ signed char sh[BINS ? kM2 : 1];
   __shared__ int rows[NS > 1 ? nk : 1];
-  __shared__ double red[NT / 64 * (BINS ? kMaxShells : 1)];
+  __shared__ double red[NT / 64];
+  __shared__ double binw[BINS ? NT / 64 * kMaxShells : 1];
   const int tid = threadIdx.x;
   const int i = pc.pairs[p] & 0xffff, j = pc.pairs[p] >> 16;
   const T* psi = static_cast<const T*>(pc.psi);
@@ -288,7 +295,6 @@ __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* 
   }
   if constexpr (NS > 1) row_table<nk, NT>(pc.cols, pc.ncol, rows);
   double s = 0.0;
-  double sb[kMaxShells] = {};
   const int sg = split ? pc.shell[pc.g0 + gl] : 0;
 #pragma unroll 1
   for (int part = 0; part < 2; ++part) {  // real, imaginary part of w
@@ -306,6 +312,7 @@ __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* 
 #pragma unroll
       for (int k = 0; k < nk; ++k) xg[k] = xf[k];
     }
+    double sb[BINS ? kMaxShells : 1] = {};
     if (tid < pc.ncol) {
       const int cd = pc.cols[tid];
       const int ky = row_k(cd & 0xff), kz = row_k(cd >> 8), r2 = ky * ky + kz * kz;
@@ -325,16 +332,27 @@ __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* 
       }
       s += m * (q0 + 2.0 * q);
     }
+    if constexpr (BINS) {
+      // bins leave the registers before the next part's transforms: each wave's
+      // sum into its own slots
+#pragma unroll
+      for (int b = 0; b < kMaxShells; ++b)
+        if (b < pc.nb) {
+          double v = sb[b];
+          for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+          double* slot = binw + (tid >> 6) * kMaxShells + b;
+          if ((tid & 63) == 0) *slot = part ? *slot + v : v;
+        }
+    }
   }
   const double scale = (i == j ? 1.0 : 2.0) * pc.dV2;
   s = block_sum(s, red);
   if (tid == 0) pc.xpart[long(gl) * pc.npairs + p] = scale * s;
   if constexpr (BINS) {
-    if (split) {
-      block_sum_bins(sb, red);
-      if (tid == 0)
-        for (int b = 0; b < pc.nb; ++b)
-          pc.xbins[(long(gl) * pc.npairs + p) * pc.nb + b] = scale * sb[b];
+    if (split && tid < pc.nb) {  // block_sum's barriers order the slots
+      double b = 0.0;
+      for (int w = 0; w < NT / 64; ++w) b += binw[w * kMaxShells + tid];
+      pc.xbins[(long(gl) * pc.npairs + p) * pc.nb + tid] = scale * b;
     }
   }
 }
@@ -344,7 +362,7 @@ __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* 
 // of (i, j), so the workgroups resident on one XCD share a handful of psi_i
 // and w_j^{(G')} in that XCD's L2.
 template <class T, int N, int KM, bool BINS>
-__global__ __launch_bounds__(pair_threads(sizeof(T), N, KM), pair_minw(sizeof(T), N)) void k_pair(
+__global__ __launch_bounds__(pair_threads(sizeof(T), N, KM), pair_minw(sizeof(T), N, BINS)) void k_pair(
     PairCell pc) {
   extern __shared__ __align__(16) char smem[];
   const long total = long(pc.npairs) * pc.gb;
