@@ -181,9 +181,9 @@ ltmp2_status with_instance(int kmax, Fn&& fn) {
   return LTMP2_EINVAL;
 }
 
-template <class T, int KM>
+template <class T, int KM, bool BINS = false>
 size_t pair_lds(int ncol) {
-  constexpr int ns = pair_slabs(sizeof(T), N, KM);
+  constexpr int ns = pair_slabs(sizeof(T), N, KM, BINS);
   return pair_lds_bytes(sizeof(T), N, KM, ns, ncol);
 }
 
@@ -220,9 +220,9 @@ ltmp2_status pair(const PairCell& pc, hipStream_t st) {
       return LTMP2_EINVAL;
     const long total = long(pc.npairs) * pc.gb;
     const dim3 grid(unsigned((total + 7) / 8 * 8));
-    const size_t lds = pair_lds<T, KM>(pc.ncol);
-    if (pc.shm2) return launch_nt(k_pair<T, N, KM, true>, grid, NT, lds, st, pc);
-    return launch_nt(k_pair<T, N, KM, false>, grid, NT, lds, st, pc);
+    if (pc.shm2)
+      return launch_nt(k_pair<T, N, KM, true>, grid, NT, pair_lds<T, KM, true>(pc.ncol), st, pc);
+    return launch_nt(k_pair<T, N, KM, false>, grid, NT, pair_lds<T, KM>(pc.ncol), st, pc);
   });
 }
 

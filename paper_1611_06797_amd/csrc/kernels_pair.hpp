@@ -96,18 +96,6 @@ __host__ __device__ constexpr size_t pair_lds_bytes(size_t es, int n, int k, int
   return es * (size_t(n / ns) * (2 * k + 1) * line_row(n) + size_t(n - n / ns) * ncol);
 }
 
-// Slabs per field: one where the whole field fits next to a second workgroup
-// (each slab costs two more barriers: 27 grid, FP32, three workgroups per CU
-// of one slab 35.7 ns per item, four of three slabs 37.4), else the fewest
-// that leave room for two workgroups, else the fewest that fit at all.
-__host__ __device__ constexpr int pair_slabs(size_t es, int n, int k) {
-  const size_t stat = 2304;  // tables and reduction scratch
-  for (size_t cap : {size_t(80) * 1024, size_t(150) * 1024})
-    for (int ns = 1; ns <= n; ++ns)
-      if (n % ns == 0 && pair_lds_bytes(es, n, k, ns, pair_cols_max(k)) + stat <= cap) return ns;
-  return n;
-}
-
 // Threads per workgroup: at least one per column; beyond that the smallest
 // workgroups that still fill the CU's wave slots from its shared memory
 // (128 against 192 threads on the 18 grid 8.8 and 8.7 ns per item, 192 against
@@ -119,6 +107,30 @@ __host__ __device__ constexpr int pair_threads(size_t es, int n, int k) {
   int nt = n <= 18 ? 128 : n <= 24 ? 192 : n <= 27 ? 256 : 512;
   if (es == 8 && n == 18) nt = 192;
   return cols > nt ? cols : nt;
+}
+
+// Static shared memory of a pair kernel, at most: v(G) and the shells by m^2,
+// the row table, one or nine FP64 slots per wave, and their alignment.
+__host__ __device__ constexpr size_t pair_static(size_t es, int n, int k, bool bins) {
+  const size_t nm2 = 2 * size_t(k) * k + 2 * k + 1, waves = pair_threads(es, n, k) / 64;
+  return 8 * nm2 + (bins ? nm2 : 1) + 4 * (2 * k + 1) + 8 * waves * (bins ? 1 + kMaxShells : 1) +
+         64;
+}
+
+// Slabs per field: one where the whole field fits next to a second workgroup
+// (each slab costs two more barriers: 27 grid, FP32, three workgroups per CU
+// of one slab 35.7 ns per item, four of three slabs 37.4), else the fewest
+// that leave room for two workgroups, else the fewest that fit at all.  The
+// split by cutoff shell needs 700 bytes more and so, on the 36 grid in FP32,
+// three slabs where two are enough without it (115 ns per item; two slabs are
+// then one workgroup per CU, 170).  On the 32 grid (|k| <= 9, FP32) the exact
+// count lets one slab pass where a rounded one took two (68 -> 63 ns).
+__host__ __device__ constexpr int pair_slabs(size_t es, int n, int k, bool bins = false) {
+  const size_t stat = pair_static(es, n, k, bins);
+  for (size_t cap : {size_t(80) * 1024 - stat, size_t(150) * 1024})
+    for (int ns = 1; ns <= n; ++ns)
+      if (n % ns == 0 && pair_lds_bytes(es, n, k, ns, pair_cols_max(k)) <= cap) return ns;
+  return n;
 }
 
 // Waves per SIMD the launch bounds ask for: the register need is about three
@@ -272,7 +284,7 @@ __device__ __forceinline__ void line_transform(const T* pa, const T* pu, const i
 // 14.2; 20 grid, |k| <= 9: 41.8 and 32.3; 12 grid, |k| <= 3, FP64: 12.3 and 9.0).
 template <class T, int N, int KM, bool BINS>
 __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* t1) {
-  constexpr int NT = pair_threads(sizeof(T), N, KM), NS = pair_slabs(sizeof(T), N, KM);
+  constexpr int NT = pair_threads(sizeof(T), N, KM), NS = pair_slabs(sizeof(T), N, KM, BINS);
   constexpr int nk = 2 * KM + 1, SP = N / NS;
   constexpr int kM2 = 2 * KM * KM + 2 * KM + 1;  // m^2 of any row triple lies below
   __shared__ double vm[kM2];
