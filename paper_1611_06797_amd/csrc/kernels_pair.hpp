@@ -102,35 +102,64 @@ __host__ __device__ constexpr size_t pair_lds_bytes(size_t es, int n, int k, int
 // 320 on the 24 grid 18.3 and 22.2, 256 against 384 on the 27 grid 36 and 45,
 // 512 against 384 on the 36 grid 94 and 109; the 12 grid would run 64 threads
 // 3 % faster when the card is full, and loses 20 % to latency when it is not).
-__host__ __device__ constexpr int pair_threads(size_t es, int n, int k) {
+// pair_threads has the last word: workgroups alone on their CU take 512.
+__host__ __device__ constexpr int pair_threads_shared(size_t es, int n, int k) {
   const int cols = (pair_cols_max(k) + 63) / 64 * 64;
   int nt = n <= 18 ? 128 : n <= 24 ? 192 : n <= 27 ? 256 : 512;
   if (es == 8 && n == 18) nt = 192;
   return cols > nt ? cols : nt;
 }
 
-// Static shared memory of a pair kernel, at most: v(G) and the shells by m^2,
-// the row table, one or nine FP64 slots per wave, and their alignment.
-__host__ __device__ constexpr size_t pair_static(size_t es, int n, int k, bool bins) {
-  const size_t nm2 = 2 * size_t(k) * k + 2 * k + 1, waves = pair_threads(es, n, k) / 64;
-  return 8 * nm2 + (bins ? nm2 : 1) + 4 * (2 * k + 1) + 8 * waves * (bins ? 1 + kMaxShells : 1) +
+// Static shared memory of a pair kernel of nt threads, at most: v(G) and the
+// shells by m^2, the row table, one or nine FP64 slots per wave, and their
+// alignment.
+__host__ __device__ constexpr size_t pair_static(int k, int nt, bool bins) {
+  const size_t nm2 = 2 * size_t(k) * k + 2 * k + 1;
+  return 8 * nm2 + (bins ? nm2 : 1) + 4 * (2 * k + 1) + nt / 64 * 8 * (bins ? 1 + kMaxShells : 1) +
          64;
 }
 
-// Slabs per field: one where the whole field fits next to a second workgroup
+// The z lines of a slab in percent of what their rounds could hold.
+__host__ __device__ constexpr int slab_fill(int n, int ns, int nt) {
+  const int lines = n / ns * n;
+  return 100 * lines / ((lines + nt - 1) / nt * nt);
+}
+
+// Slabs per field.  One where the whole field fits next to a second workgroup
 // (each slab costs two more barriers: 27 grid, FP32, three workgroups per CU
 // of one slab 35.7 ns per item, four of three slabs 37.4), else the fewest
-// that leave room for two workgroups, else the fewest that fit at all.  The
-// split by cutoff shell needs 700 bytes more and so, on the 36 grid in FP32,
-// three slabs where two are enough without it (115 ns per item; two slabs are
-// then one workgroup per CU, 170).  On the 32 grid (|k| <= 9, FP32) the exact
-// count lets one slab pass where a rounded one took two (68 -> 63 ns).
+// that leave room for two workgroups and whose z lines fill more than 60 % of
+// their rounds (FP64: 25 grid 110 ns in five slabs of 125 lines for 256
+// threads, 101 in one slab; 27 grid, |k| <= 10, nine slabs of 81 lines 346,
+// one slab 134; 30 grid, |k| <= 9, fifteen slabs 451, one 164), else the fewest
+// that fit at all.  The long lines of FP64 leave few waves per workgroup, so
+// there a third workgroup comes first, if its slabs are one round each (24
+// grid, three slabs of 192 lines 60 ns, one slab 66, two slabs 75).  The split
+// by cutoff shell needs 700 bytes more and so, on the 36 grid in FP32, three
+// slabs where two are enough without it (115 ns per item; two slabs are then
+// one workgroup per CU, 170).  On the 32 grid (|k| <= 9, FP32) the exact count
+// lets one slab pass where a rounded one took two (68 -> 63 ns).
 __host__ __device__ constexpr int pair_slabs(size_t es, int n, int k, bool bins = false) {
-  const size_t stat = pair_static(es, n, k, bins);
-  for (size_t cap : {size_t(80) * 1024 - stat, size_t(150) * 1024})
+  const int nt = pair_threads_shared(es, n, k), cols = pair_cols_max(k);
+  const size_t stat = pair_static(k, nt, bins);
+  for (int wgs = es == 8 ? 3 : 2; wgs >= 2; --wgs)
     for (int ns = 1; ns <= n; ++ns)
-      if (n % ns == 0 && pair_lds_bytes(es, n, k, ns, pair_cols_max(k)) <= cap) return ns;
+      if (n % ns == 0 && (ns == 1 || slab_fill(n, ns, nt) >= 60) &&
+          (ns == 1 || wgs == 2 || n / ns * n <= nt) &&
+          pair_lds_bytes(es, n, k, ns, cols) + stat <= size_t(160) * 1024 / wgs)
+        return ns;
+  for (int ns = 1; ns <= n; ++ns)
+    if (n % ns == 0 && pair_lds_bytes(es, n, k, ns, cols) <= size_t(150) * 1024) return ns;
   return n;
+}
+
+// A workgroup that has its CU to itself brings all the waves its registers
+// allow (FP64: 24 grid, |k| <= 10, 384 threads 95 ns, 512 threads 90; 25 grid 256
+// threads 125, 512 threads 101).
+__host__ __device__ constexpr int pair_threads(size_t es, int n, int k) {
+  const int nt = pair_threads_shared(es, n, k);
+  const size_t lds = pair_lds_bytes(es, n, k, pair_slabs(es, n, k), pair_cols_max(k));
+  return es == 8 && lds + pair_static(k, nt, false) > size_t(80) * 1024 && nt < 512 ? 512 : nt;
 }
 
 // Waves per SIMD the launch bounds ask for: the register need is about three

@@ -36,7 +36,8 @@ template <int... N> void all(std::integer_sequence<int, N...>) {
             if (n % ns == 0)
               printf("%d %d %d %d %d %d %d %zu %zu\n", es, n, k, bins, ns,
                      ns == pair_slabs(es, n, k, bins), pair_threads(es, n, k),
-                     pair_lds_bytes(es, n, k, ns, pair_cols_max(k)), pair_static(es, n, k, bins));
+                     pair_lds_bytes(es, n, k, ns, pair_cols_max(k)),
+                     pair_static(k, pair_threads(es, n, k), bins));
       }
   };
   (grid(N), ...);
@@ -110,3 +111,14 @@ def test_static_shared_memory_is_counted(kernels, slabs):
         assert lds <= 150 * 1024 and nt % 64 == 0 and nt <= 512, key
         seen += 1
     assert seen >= 48
+
+
+def test_slabs_keep_their_threads_busy(slabs):
+    """A field is not cut so thin that a slab's z lines leave most of its threads idle: FP64
+    fields of the 25, 27 and 30 grids once went in five to fifteen slabs of 60 to 125 lines."""
+    for key, rows in slabs.items():
+        ns, _, nt, lds, _ = [x for x in rows if x[1]][0]
+        lines = key[1] // ns * key[1]
+        fewer = [x for x in rows if x[0] < ns and x[3] <= 150 * 1024]
+        if fewer:  # more slabs than shared memory asks for
+            assert lines * 100 >= 60 * -(-lines // nt) * nt, (key, ns, nt)
