@@ -195,8 +195,10 @@ ltmp2_status real_forward(const T* a, long ld, int nocc, long items, const int* 
     constexpr int KM = decltype(km)::value, NT = pair_threads(sizeof(T), N, KM);
     if (ncol < 1 || ncol > pair_cols_max(KM)) return LTMP2_EINVAL;
     const size_t lds = std::max(pair_lds<T, KM>(ncol), sizeof(T) * (2 * KM + 1) * ncol);
-    return launch_nt(k_real_forward<T, N, KM, OVERLAP>, dim3(unsigned((items + 7) / 8 * 8)), NT,
-                     lds, st, a, ld, nocc, items, cols, ncol, gdesc, nh, kmax, scale, out);
+    return launch_ranges(items, NT, [&](long first, long count) {
+      return launch_nt(k_real_forward<T, N, KM, OVERLAP>, dim3(launch_blocks(count)), NT, lds, st,
+                       a, ld, nocc, first, count, cols, ncol, gdesc, nh, kmax, scale, out);
+    });
   });
 }
 template <class T>
@@ -218,11 +220,14 @@ ltmp2_status pair(const PairCell& pc, hipStream_t st) {
     constexpr int KM = decltype(km)::value, NT = pair_threads(sizeof(T), N, KM);
     if (pc.ncol < 1 || pc.ncol > pair_cols_max(KM) || pc.nm2 > 2 * KM * KM + 2 * KM + 1)
       return LTMP2_EINVAL;
-    const long total = long(pc.npairs) * pc.gb;
-    const dim3 grid(unsigned((total + 7) / 8 * 8));
-    if (pc.shm2)
-      return launch_nt(k_pair<T, N, KM, true>, grid, NT, pair_lds<T, KM, true>(pc.ncol), st, pc);
-    return launch_nt(k_pair<T, N, KM, false>, grid, NT, pair_lds<T, KM>(pc.ncol), st, pc);
+    return launch_ranges(long(pc.npairs) * pc.gb, NT, [&](long first, long count) {
+      const dim3 grid(launch_blocks(count));
+      if (pc.shm2)
+        return launch_nt(k_pair<T, N, KM, true>, grid, NT, pair_lds<T, KM, true>(pc.ncol), st, pc,
+                         first, count);
+      return launch_nt(k_pair<T, N, KM, false>, grid, NT, pair_lds<T, KM>(pc.ncol), st, pc, first,
+                       count);
+    });
   });
 }
 
@@ -233,9 +238,10 @@ ltmp2_status pair_multi(const PairCell* cells, const long* prefix, int ncells, l
   return with_instance(kmax_max, [&](auto km) -> ltmp2_status {
     constexpr int KM = decltype(km)::value, NT = pair_threads(sizeof(T), N, KM);
     if (ncol_max < 1 || ncol_max > pair_cols_max(KM)) return LTMP2_EINVAL;
-    const dim3 grid(unsigned((total + 7) / 8 * 8));
-    return launch_nt(k_pair_multi<T, N, KM>, grid, NT, pair_lds<T, KM>(ncol_max), st, cells,
-                     prefix, ncells);
+    return launch_ranges(total, NT, [&](long first, long count) {
+      return launch_nt(k_pair_multi<T, N, KM>, dim3(launch_blocks(count)), NT,
+                       pair_lds<T, KM>(ncol_max), st, cells, prefix, ncells, first, count);
+    });
   });
 }
 

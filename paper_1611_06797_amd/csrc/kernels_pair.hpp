@@ -33,6 +33,7 @@
 // 112 -> 94; in FP64, 15: 19.4 -> 13.4, 20: 56 -> 38, 24: 77 -> 68, 27:
 // 189 -> 112.
 #pragma once
+#include "launch_items.hpp"
 #include "rfft.hpp"
 #include "transforms.hpp"
 
@@ -398,35 +399,34 @@ __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* 
   }
 }
 
-// One cell: workgroups are dispatched round-robin over the 8 XCDs; each XCD
-// gets a contiguous range of the (G', pair) list, whose pairs come in blocks
-// of (i, j), so the workgroups resident on one XCD share a handful of psi_i
-// and w_j^{(G')} in that XCD's L2.
+// One cell, items [first, first + count) of its (G', pair) list: the pairs come
+// in blocks of (i, j) and each XCD takes a contiguous range, so the workgroups
+// resident on one XCD share a handful of psi_i and w_j^{(G')} in its L2.
 template <class T, int N, int KM, bool BINS>
 __global__ __launch_bounds__(pair_threads(sizeof(T), N, KM), pair_minw(sizeof(T), N, BINS)) void k_pair(
-    PairCell pc) {
+    PairCell pc, long first, long count) {
   extern __shared__ __align__(16) char smem[];
-  const long total = long(pc.npairs) * pc.gb;
-  const long per_xcd = (total + 7) / 8;
-  const long t = long(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (t >= total) return;
+  const long b = block_item(blockIdx.x, count);
+  if (b < 0) return;
+  const long t = first + b;
   const int gl = int(t / pc.npairs);
   pair_item<T, N, KM, BINS>(pc, gl, int(t - long(gl) * pc.npairs), reinterpret_cast<T*>(smem));
 }
 
 // Several cells of the same grid and kept-set instance in one launch: the
 // work list is the concatenation of every cell's (G', pair) items (prefix[c] =
-// first item of cell c), one item per workgroup, in XCD-contiguous ranges.
+// first item of cell c), of which it takes [first, first + count), one item per
+// workgroup, in XCD-contiguous ranges.
 template <class T, int N, int KM>
 __global__ __launch_bounds__(pair_threads(sizeof(T), N, KM),
                              pair_minw(sizeof(T), N)) void k_pair_multi(const PairCell* __restrict__ cells,
                                                                         const long* __restrict__ prefix,
-                                                                        int ncells) {
+                                                                        int ncells, long first,
+                                                                        long count) {
   extern __shared__ __align__(16) char smem[];
-  const long total = prefix[ncells];
-  const long per_xcd = (total + 7) / 8;
-  const long t = long(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (blockIdx.x / 8 >= per_xcd || t >= total) return;
+  const long b = block_item(blockIdx.x, count);
+  if (b < 0) return;
+  const long t = first + b;
   int lo = 0, hi = ncells - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) / 2;
@@ -459,16 +459,16 @@ __global__ __launch_bounds__(pair_threads(sizeof(T), N, KM),
 // overlap densities on the 36 grid 55 -> 15.5 ms.
 template <class T, int N, int KM, bool OVERLAP>
 __global__ __launch_bounds__(pair_threads(sizeof(T), N, KM), pair_minw(sizeof(T), N))
-void k_real_forward(const T* __restrict__ a, long ld, int nocc, long items,
+void k_real_forward(const T* __restrict__ a, long ld, int nocc, long first, long count,
                     const int* __restrict__ cols, int ncol, const int* __restrict__ gdesc, int nh,
                     int kmax, double scale, cplx<T>* __restrict__ out) {
   constexpr int NT = pair_threads(sizeof(T), N, KM), NS = pair_slabs(sizeof(T), N, KM);
   constexpr int nk = 2 * KM + 1, SP = N / NS;
   extern __shared__ __align__(16) char smem[];
   __shared__ int rows[nk];
-  const long per_xcd = (items + 7) / 8;
-  const long it = long(blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
-  if (it >= items) return;
+  const long b = block_item(blockIdx.x, count);
+  if (b < 0) return;
+  const long it = first + b;
   T* t1 = reinterpret_cast<T*>(smem);
   T* t2 = t1 + SP * nk * line_row(N);
   const int tid = threadIdx.x;
