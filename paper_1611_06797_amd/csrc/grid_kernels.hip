@@ -121,22 +121,30 @@ ltmp2_status hartree(const cplx<T>* h, long ld, const int* gdesc, int ng, const 
   return by_opt<HartreeF<T>::template F>(ng, h, ld, gdesc, ng, v, kmax, dV, g0, gb, pdh, st);
 }
 
-template <class T, int K>
+template <class T, int K, bool WIDE = false>
 ltmp2_status wstates_window_launch(const T* P, int npw, const void* tab, int nitems, double scale,
                                    T* w, long ld, hipStream_t st) {
-  using W = WstShape<T, N, K>;
-  return launch_nt(k_wstates_real<T, N, K>, dim3(unsigned(2L * nitems / W::F)), W::NT, W::lds(npw),
-                   st, P, npw, static_cast<const unsigned short*>(tab), scale, w, ld);
+  using W = WstShape<T, N, K, WIDE>;
+  if constexpr (!W::holds_all)
+    if (W::lds(npw) > kLdsCap)
+      return wstates_window_launch<T, K, true>(P, npw, tab, nitems, scale, w, ld, st);
+  return launch_nt(k_wstates_real<T, N, K, WIDE>, dim3(unsigned(2L * nitems / W::F)), W::NT,
+                   W::lds(npw), st, P, npw, static_cast<const unsigned short*>(tab), scale, w, ld);
 }
 
 // Window instance of the transformed states for a cell (-1: the general kernel,
-// also for a set so far from a sphere that it leaves no room next to the field)
+// also for a set that has so many more vectors than a sphere of its largest
+// index that they leave no room next to the field)
+template <class T, int K>
+constexpr bool wstates_holds(int npw) {
+  static_assert(WstShape<T, N, K, true>::holds_all);
+  return WstShape<T, N, K>::lds(npw) <= kLdsCap || WstShape<T, N, K, true>::lds(npw) <= kLdsCap;
+}
 template <class T>
 int wstates_kept(int kmax, int npw) {
   constexpr int ko = korb_win(N), kl = ko < 2 ? ko : ko - 1;
   const int win = wstates_window(N, kmax);
-  const size_t lds = win == ko ? WstShape<T, N, ko>::lds(npw) : WstShape<T, N, kl>::lds(npw);
-  return lds <= kLdsCap ? win : -1;
+  return (win == ko ? wstates_holds<T, ko>(npw) : wstates_holds<T, kl>(npw)) ? win : -1;
 }
 
 template <class T>

@@ -26,24 +26,44 @@
 
 namespace ltmp2 {
 
+// Vectors of the largest sphere whose largest index is k: |m|^2 < (k + 1)^2, a
+// quarter more than the sphere of radius k at the sizes here.
+__host__ __device__ constexpr int sphere_max(int k) {
+  int c = 0;
+  for (int x = 0; x <= k; ++x)
+    for (int y = 0; y <= k; ++y) {
+      int z = k;
+      while (z >= 0 && x * x + y * y + z * z >= (k + 1) * (k + 1)) --z;
+      c += (x ? 2 : 1) * (y ? 2 : 1) * (z >= 0 ? 2 * z + 1 : 0);
+    }
+  return c;
+}
+
 // Fields per workgroup, slabs of x planes per field and threads.  Two fields
 // while three workgroups still fit a CU, else one.  One slab where the whole
 // field fits a CU (27 grid, FP64: 716 us for 12160 states, three slabs and two
 // workgroups 801), else the fewest that leave room for two workgroups (36 grid,
 // FP32: 1750 us for 12320 states with three, 1911 with two slabs and one
-// workgroup).  The coefficients are counted for a full sphere.
-template <class T, int N, int K>
+// workgroup).  That is judged at a sphere of radius K.  Where the largest sphere
+// of the window would not fit then, those that do not run in the WIDE form, in
+// more slabs (40 grid, FP64, K = 13: 10059 vectors 0.97 ms for 1200 states in
+// eight slabs, 3.6 by the general kernel; 9939 vectors 0.61 in five slabs).
+template <class T, int N, int K, bool WIDE = false>
 struct WstShape {
   static constexpr int R = slab_row(N);
-  static constexpr size_t bytes(int f, int s) {
-    return sizeof(cplx<T>) * f * (size_t(N / s) * (K + 1) * R + 21 * size_t(K) * K * K / 10 + 2);
+  static constexpr size_t bytes(int f, int s, int npw) {
+    return sizeof(cplx<T>) * f * (size_t(N / s) * (K + 1) * R + (npw + 1) / 2 + 1);
   }
-  static constexpr int F = bytes(2, 1) <= 52 * 1024 ? 2 : 1;
+  static constexpr int radius_k = 21 * K * K * K / 5;  // vectors of a sphere of radius K
+  static constexpr int F = bytes(2, 1, radius_k) <= 52 * 1024 ? 2 : 1;
+  static constexpr bool fits(int s, size_t cap) {
+    return bytes(F, s, radius_k) <= cap && (!WIDE || bytes(F, s, sphere_max(K)) <= 150 * 1024);
+  }
   static constexpr int slabs() {
-    if (bytes(F, 1) <= 148 * 1024) return 1;
+    if (fits(1, 148 * 1024)) return 1;
     for (size_t cap : {size_t(78) * 1024, size_t(148) * 1024})
       for (int s = 2; s < N; ++s)
-        if (N % s == 0 && bytes(F, s) <= cap) return s;
+        if (N % s == 0 && fits(s, cap)) return s;
     return N;
   }
   static constexpr int S = slabs(), SP = N / S;
@@ -52,20 +72,19 @@ struct WstShape {
   static constexpr int NT = zlines <= 128 ? 128 : zlines >= 512 ? 512 : (zlines + 63) / 64 * 64;
   // waves per SIMD: registers for a complex line and its transform
   static constexpr int MINW = sizeof(T) == 4 ? (N <= 20 ? 4 : N <= 27 ? 3 : 2) : 2;
-  static size_t lds(int npw) {
-    return sizeof(cplx<T>) * F * (size_t(SP) * (K + 1) * R + (npw + 1) / 2 + 1);
-  }
+  static constexpr size_t lds(int npw) { return bytes(F, S, npw); }
+  static constexpr bool holds_all = bytes(F, S, sphere_max(K)) <= 150 * 1024;
 };
 
 // wx [2 K + 1][(K + 1)(2 K + 1)]: for kx and slot (kz, ky), the index of the
 // coefficient pair in a row of P (0: G = 0; (npw + 1) / 2: none), bit 15 set
 // where its conjugate is meant (sets that fit shared memory have fewer than 2^15
 // pairs).
-template <class T, int N, int K>
-__global__ __launch_bounds__((WstShape<T, N, K>::NT), (WstShape<T, N, K>::MINW))
+template <class T, int N, int K, bool WIDE>
+__global__ __launch_bounds__((WstShape<T, N, K, WIDE>::NT), (WstShape<T, N, K, WIDE>::MINW))
 void k_wstates_real(const T* __restrict__ P, int npw, const unsigned short* __restrict__ wx,
                     double scale, T* __restrict__ w, long ld) {
-  using W = WstShape<T, N, K>;
+  using W = WstShape<T, N, K, WIDE>;
   constexpr int F = W::F, SP = W::SP, R = W::R, NT = W::NT, nk = W::nk;
   extern __shared__ __align__(16) char smem[];
   cplx<T>* t = reinterpret_cast<cplx<T>*>(smem);  // [F][SP][K + 1][R]
