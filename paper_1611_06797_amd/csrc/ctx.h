@@ -93,13 +93,14 @@ struct ltmp2_ctx {
   int* d_cstart = nullptr;
   int* d_ckx = nullptr;
   void* d_wtab = nullptr;         // coefficients of the transformed states (GridOps::wstates)
+  int wtab_k = 0;
   int* d_gdesc = nullptr;
   int* d_pairs = nullptr;
   int* d_cols = nullptr;          // [ncol] columns of the pair transforms (PairCell)
-  signed char* d_shm2 = nullptr;  // [nm2] spheres by m^2 (cutoff extrapolation)
+  signed char* d_shm2 = nullptr;  // [m2lim + 1] spheres by m^2 (cutoff extrapolation)
   int ncol = 0, nm2 = 0, m2lim = 0;  // PairCell
   double vden = 0.0;
-  double* d_v = nullptr;
+  double* d_v = nullptr;          // [nh] v(G') of H
   double* d_fo = nullptr;  // [ntau][no]
   double* d_fv = nullptr;  // [ntau][nv]
 
@@ -122,7 +123,7 @@ struct ltmp2_ctx {
   int nb = 0;
   double alpha = 1.05;
   std::vector<double> eaux_n;    // [nb] cutoffs eaux / alpha^(n-1)
-  signed char* d_shell = nullptr;  // [ng] spheres containing each vector
+  signed char* d_shell = nullptr;  // [nh] spheres containing each vector of H
   double* d_pdb = nullptr;     // [nh][nb] direct-term bins per G'
   double* d_xb = nullptr;      // [nh][npairs][nb] exchange bins per (G', pair)
   double* d_xrowb = nullptr;   // [nh][nb]
@@ -158,7 +159,7 @@ ltmp2_status run_exchange(ltmp2_ctx* c, int itau, int g_first, int g_count);
 // Pieces of run_exchange used by batched execution.
 PairCell pair_cell(const ltmp2_ctx* c, int g0, int gb);
 // Occupied orbitals in the pair transforms' order: kept, or in the chi scratch.
-inline void* occupied(const ltmp2_ctx* c) { return c->d_psiz ? c->d_psiz : c->d_chihat; }
+inline void* occupied(const ltmp2_ctx* c) { return c->d_psiz ? c->d_psiz : c->d_chi; }
 ltmp2_status exchange_block_prepare(ltmp2_ctx* c, int itau, int g0, int gb);
 ltmp2_status exchange_reduce(ltmp2_ctx* c, int itau, int g_first, int g_count);
 ltmp2_status setup_cell(ltmp2_ctx* c, const int32_t* miller, const double* eps,

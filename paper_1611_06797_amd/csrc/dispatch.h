@@ -33,9 +33,9 @@ struct GridOps {
   ltmp2_status (*chi_cols)(const cplx<T>* chihat, long ld, const int* gdesc, int ng, int nh,
                            const double* v, int kmax, double dV, double* pd,
                            cplx<double>* chi_out, ShellBins bins, hipStream_t st);
-  // tab: wx of kernels_wstates.hpp for the window wstates_kept(sc.kmax, npw), wq
-  // of k_wstates where that is -1
-  ltmp2_status (*wstates)(const T* P, int npw, const void* tab, SphereCols sc, int nitems,
+  // tab: wx of kernels_wstates.hpp by indices up to kt, the window
+  // wstates_kept(sc.kmax, npw) or sc.kmax; wq of k_wstates where that window is -1
+  ltmp2_status (*wstates)(const T* P, int npw, const void* tab, int kt, SphereCols sc, int nitems,
                           double scale, T* w, long ld, hipStream_t st);
   // pair transforms of one block of outer vectors of a cell
   ltmp2_status (*pair)(const PairCell& pc, hipStream_t st);

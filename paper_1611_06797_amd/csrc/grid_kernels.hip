@@ -121,20 +121,25 @@ ltmp2_status hartree(const cplx<T>* h, long ld, const int* gdesc, int ng, const 
   return by_opt<HartreeF<T>::template F>(ng, h, ld, gdesc, ng, v, kmax, dV, g0, gb, pdh, st);
 }
 
-template <class T, int K, bool WIDE = false>
-ltmp2_status wstates_window_launch(const T* P, int npw, const void* tab, int nitems, double scale,
-                                   T* w, long ld, hipStream_t st) {
+template <class T, int K, bool WIDE = false, bool SMALL = false>
+ltmp2_status wstates_window_launch(const T* P, int npw, const void* tab, int kt, int nitems,
+                                   double scale, T* w, long ld, hipStream_t st) {
   using W = WstShape<T, N, K, WIDE>;
   if constexpr (!W::holds_all)
     if (W::lds(npw) > kLdsCap)
-      return wstates_window_launch<T, K, true>(P, npw, tab, nitems, scale, w, ld, st);
-  return launch_nt(k_wstates_real<T, N, K, WIDE>, dim3(unsigned(2L * nitems / W::F)), W::NT,
-                   W::lds(npw), st, P, npw, static_cast<const unsigned short*>(tab), scale, w, ld);
+      return wstates_window_launch<T, K, true>(P, npw, tab, kt, nitems, scale, w, ld, st);
+  if constexpr (K < korb_win(N) && !SMALL)
+    if (kt < K)
+      return wstates_window_launch<T, K, WIDE, true>(P, npw, tab, kt, nitems, scale, w, ld, st);
+  return launch_nt(k_wstates_real<T, N, K, WIDE, SMALL>, dim3(unsigned(2L * nitems / W::F)), W::NT,
+                   W::lds(npw), st, P, npw, static_cast<const unsigned short*>(tab), kt, scale, w,
+                   ld);
 }
 
 // Window instance of the transformed states for a cell (-1: the general kernel,
 // also for a set that has so many more vectors than a sphere of its largest
-// index that they leave no room next to the field)
+// index that they leave no room next to the field, or so few that the table by
+// wavevector is larger than five bytes for each)
 template <class T, int K>
 constexpr bool wstates_holds(int npw) {
   static_assert(WstShape<T, N, K, true>::holds_all);
@@ -143,17 +148,20 @@ constexpr bool wstates_holds(int npw) {
 template <class T>
 int wstates_kept(int kmax, int npw) {
   constexpr int ko = korb_win(N), kl = ko < 2 ? ko : ko - 1;
-  const int win = wstates_window(N, kmax);
+  const int win = wstates_window(N, kmax), nk = 2 * kmax + 1;
+  if (2 * nk * nk * (kmax + 1) > 5 * npw + 4) return -1;
   return (win == ko ? wstates_holds<T, ko>(npw) : wstates_holds<T, kl>(npw)) ? win : -1;
 }
 
 template <class T>
-ltmp2_status wstates(const T* P, int npw, const void* tab, SphereCols sc, int nitems, double scale,
-                     T* w, long ld, hipStream_t st) {
+ltmp2_status wstates(const T* P, int npw, const void* tab, int kt, SphereCols sc, int nitems,
+                     double scale, T* w, long ld, hipStream_t st) {
   constexpr int ko = korb_win(N), kl = ko < 2 ? ko : ko - 1;
   const int win = wstates_kept<T>(sc.kmax, npw);
-  if (win == ko) return wstates_window_launch<T, ko>(P, npw, tab, nitems, scale, w, ld, st);
-  if (win == kl) return wstates_window_launch<T, kl>(P, npw, tab, nitems, scale, w, ld, st);
+  if (win == ko)
+    return wstates_window_launch<T, ko>(P, npw, tab, kt, nitems, scale, w, ld, st);
+  if (win == kl)
+    return wstates_window_launch<T, kl>(P, npw, tab, kt, nitems, scale, w, ld, st);
   // the largest slab tile that lets four workgroups share a CU, unless two
   // workgroups per CU would allow more than twice that tile
   const int nk = 2 * sc.kmax + 1;
@@ -288,8 +296,8 @@ ltmp2_status plane_order(const T* in, long ld, int nocc, T* out, hipStream_t st)
   template ltmp2_status chi_cols<T>(const cplx<T>*, long, const int*, int, int, const double*, \
                                     int, double, double*, cplx<double>*, ShellBins,            \
                                     hipStream_t);                                              \
-  template ltmp2_status wstates<T>(const T*, int, const void*, SphereCols, int, double, T*, long,\
-                                   hipStream_t);                                               \
+  template ltmp2_status wstates<T>(const T*, int, const void*, int, SphereCols, int, double, T*,\
+                                   long, hipStream_t);                                               \
   template int wstates_kept<T>(int, int);                                                      \
   template ltmp2_status pair<T>(const PairCell&, hipStream_t);                                 \
   template ltmp2_status pair_multi<T>(const PairCell*, const long*, int, long, int, int,       \

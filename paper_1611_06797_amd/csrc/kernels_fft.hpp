@@ -36,7 +36,8 @@ __global__ __launch_bounds__(kThreads) void k_orbitals(const cplx<double>* __res
 // ---------------------------------------------------------------------------
 // Second pass (columns) and the Coulomb trace: for G' = H[g],
 //   chi(G, G') = dV sum_r e^{-iG.r} chihat(r, G'),  G in the full set,
-//   pd[g] = v(G') sum_G v(G) |chi(G, G')|^2.
+//   pd[g] = v(G') sum_G v(G) |chi(G, G')|^2,
+// v and the shells of the bins given for H (those of -H are the same).
 // Optionally stores chi(G, G') for G' in H and, by chi(-G, -G') =
 // conj chi(G, G') (real chi(r, r')), for G' in -H:  out[G][G'] (ng x ng),
 // and the same sum split by auxiliary cutoff shell (bins.out [n_h][nb]).
@@ -75,9 +76,10 @@ __global__ __launch_bounds__(kThreads) void k_chi_cols(const cplx<T>* __restrict
     const int o = threadIdx.x + t * kThreads;
     if (o < ng) {
       const double re = dV * double(acc[0][t].x), im = dV * double(acc[0][t].y);
-      const double term = v[o] * (re * re + im * im);
+      const int oh = o < nh ? o : o - nh;
+      const double term = v[oh] * (re * re + im * im);
       s += term;
-      if (bins.shell) bin_add(sb, min(int(bins.shell[o]), sg) - 1, term);
+      if (bins.shell) bin_add(sb, min(int(bins.shell[oh]), sg) - 1, term);
       if (chi_out) {
         const int on = (o < nh) ? o + nh : o - nh;
         chi_out[long(o) * ng + g] = {re, im};
@@ -151,7 +153,7 @@ __global__ __launch_bounds__(kThreads) void k_hartree(const cplx<T>* __restrict_
     const int o = threadIdx.x + t * kThreads;
     if (o < ng) {
       const double re = dV * double(acc[0][t].x), im = dV * double(acc[0][t].y);
-      s += v[o] * (re * re + im * im);
+      s += v[o < ng / 2 ? o : o - ng / 2] * (re * re + im * im);
     }
   }
   s = block_sum(s, red);

@@ -54,7 +54,7 @@ struct PairCell {
   int nocc, npairs, gb, kmax, ncol, nm2, m2lim;
   double dV2, vden;
   // optional split by auxiliary cutoff shell (ShellBins): number of spheres
-  // by m^2 (1 outside the set, where v = 0), the shells of the outer vectors
+  // by m^2 <= m2lim (beyond, v = 0), the shells of the outer vectors
   // from the block's first one on, and xbins [gb][npairs][nb]
   const signed char* shm2 = nullptr;   // nullptr: no split
   const signed char* shell = nullptr;  // shell of G' = shell[g0 + gl]
@@ -333,7 +333,7 @@ __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* 
   for (int k = tid; k < pc.nm2; k += NT) {
     vm[k] = k >= 1 && k <= pc.m2lim ? 4.0 * M_PI / (pc.vden * double(k)) : 0.0;
     if constexpr (BINS)
-      if (split) sh[k] = pc.shm2[k];
+      if (split) sh[k] = k <= pc.m2lim ? pc.shm2[k] : 1;
   }
   if constexpr (NS > 1) row_table<nk, NT>(pc.cols, pc.ncol, rows);
   double s = 0.0;

@@ -76,13 +76,15 @@ struct WstShape {
   static constexpr bool holds_all = bytes(F, S, sphere_max(K)) <= 150 * 1024;
 };
 
-// wx [2 K + 1][(K + 1)(2 K + 1)]: for kx and slot (kz, ky), the index of the
-// coefficient pair in a row of P (0: G = 0; (npw + 1) / 2: none), bit 15 set
-// where its conjugate is meant (sets that fit shared memory have fewer than 2^15
-// pairs).
-template <class T, int N, int K, bool WIDE>
+// wx [2 kt + 1][kt + 1][2 kt + 1] + one entry: for (kx, kz, ky), the index of the
+// coefficient pair in a row of P (0: G = 0; (npw + 1) / 2: none, as the last entry
+// says), bit 15 set where its conjugate is meant (sets that fit shared memory
+// have fewer than 2^15 pairs).  kt = K, or the set's own largest index below it
+// (SMALL: contexts under a workspace cap; its range checks take 1 to 7 % of the
+// kernel's time).
+template <class T, int N, int K, bool WIDE, bool SMALL>
 __global__ __launch_bounds__((WstShape<T, N, K, WIDE>::NT), (WstShape<T, N, K, WIDE>::MINW))
-void k_wstates_real(const T* __restrict__ P, int npw, const unsigned short* __restrict__ wx,
+void k_wstates_real(const T* __restrict__ P, int npw, const unsigned short* __restrict__ wx, int kt,
                     double scale, T* __restrict__ w, long ld) {
   using W = WstShape<T, N, K, WIDE>;
   constexpr int F = W::F, SP = W::SP, R = W::R, NT = W::NT, nk = W::nk;
@@ -117,20 +119,24 @@ void k_wstates_real(const T* __restrict__ P, int npw, const unsigned short* __re
     // x: slot (kz, ky) of a field, all planes from registers
     for (int l = tid; l < F * W::NSLOT; l += NT) {
       const int f = l / W::NSLOT, sl = l - f * W::NSLOT;
+      const int kz = sl / nk, ky = sl - kz * nk - K;
+      const int k = SMALL ? kt : K, plane = (k + 1) * (2 * k + 1);
+      const int row = k * plane + kz * (2 * k + 1) + ky + k;
+      const bool in = !SMALL || (kz <= k && ky >= -k && ky <= k);
       cplx<T> v[N];
 #pragma unroll
       for (int x = 0; x < N; ++x) {
         const int kx = x <= N / 2 ? x : x - N;
         v[x] = {T(0), T(0)};
         if (kx >= -K && kx <= K) {
-          const int code = wx[(kx + K) * W::NSLOT + sl];
+          const int at = row + kx * plane;
+          const int code = wx[!SMALL || (in && kx >= -k && kx <= k) ? at : (2 * k + 1) * plane];
           v[x] = co[f * nce + (code & 0x7fff)];
           v[x].y = code & 0x8000 ? -v[x].y : v[x].y;
         }
       }
       Fft<T, 1, N>::run(v);
-      const int kz = sl / nk;
-      cplx<T>* d = t + (f * SP * (K + 1) + kz) * R + (sl - kz * nk);
+      cplx<T>* d = t + (f * SP * (K + 1) + kz) * R + ky + K;
       if constexpr (W::S == 1) {
 #pragma unroll
         for (int x = 0; x < N; ++x) d[x * (K + 1) * R] = v[x];

@@ -385,15 +385,15 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
     }
   c->kmax_aux = km;
   std::vector<int> gdesc(c->ng);
-  std::vector<double> v(c->ng);
+  std::vector<double> v(c->nh);  // of H; v(-G) = v(G)
   for (int k = 0; k < c->ng; ++k) {
     const int x = c->aux[3 * k], y = c->aux[3 * k + 1], z = c->aux[3 * k + 2];
     gdesc[k] = pack_g(((x % n) + n) % n, y + km, z + km);
-    v[k] = 4.0 * M_PI / (c->omega * b * b * double(x * x + y * y + z * z));
+    if (k < c->nh) v[k] = 4.0 * M_PI / (c->omega * b * b * double(x * x + y * y + z * z));
   }
 
   // internal cutoff extrapolation: number of nested spheres containing each
-  // auxiliary vector (the same inclusive integer test as the auxiliary set)
+  // vector of H (the same inclusive integer test as the auxiliary set)
   std::vector<signed char> shell, shm2;
   std::vector<int> lims;
   if (P.n_extrap > 0) {
@@ -405,8 +405,8 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
       c->eaux_n[q] = P.eaux / std::pow(c->alpha, q);
       lims[q] = int(std::floor(2.0 * c->eaux_n[q] / (b * b) + 1e-9));
     }
-    shell.resize(c->ng);
-    for (int k = 0; k < c->ng; ++k) {
+    shell.resize(c->nh);
+    for (int k = 0; k < c->nh; ++k) {
       const int x = c->aux[3 * k], y = c->aux[3 * k + 1], z = c->aux[3 * k + 2];
       const int m2 = x * x + y * y + z * z;
       int sh = 0;
@@ -429,8 +429,8 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
   c->m2lim = lim;
   c->vden = c->omega * b * b;
   if (c->nb) {
-    shm2.assign(c->nm2, 1);
-    for (int m2 = 1; m2 < c->nm2 && m2 <= lim; ++m2) {
+    shm2.assign(lim + 1, 1);
+    for (int m2 = 1; m2 <= lim; ++m2) {
       int sh = 0;
       while (sh < c->nb && m2 <= lims[sh]) ++sh;
       shm2[m2] = static_cast<signed char>(sh);
@@ -476,12 +476,15 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
   if (zero_idx < 0 || nq != c->npw)
     return fail(nullptr, LTMP2_EINVAL, "basis must contain G = 0 and be symmetric");
   // table of the transformed states (GridOps::wstates): by (kx, kz >= 0, ky) for
-  // the kernels of a sphere window, else by sphere entry
+  // the kernels of a sphere window, else by sphere entry.  Under a workspace cap
+  // the former covers no more than the sphere's own indices: five bytes per plane
+  // wave hold either table, as in the footprints that caps were first chosen for
   const int kw = P.prec == LTMP2_FP64 ? grid_ops<double>(n)->wstates_kept(ko, c->npw)
                                       : grid_ops<float>(n)->wstates_kept(ko, c->npw);
-  const int nkw = 2 * kw + 1, slots = (kw + 1) * nkw;
+  const int kt = P.workspace_cap ? ko : kw, nkw = 2 * kt + 1, slots = (kt + 1) * nkw;
+  c->wtab_k = kt;
   std::vector<int> wq(kw < 0 ? size_t(c->npw) : 0);
-  std::vector<unsigned short> wx(kw < 0 ? 0 : size_t(nkw) * slots,
+  std::vector<unsigned short> wx(kw < 0 ? 0 : size_t(nkw) * slots + 1,
                                  static_cast<unsigned short>((c->npw + 1) / 2));
   for (int e = 0; e < c->npw; ++e) {
     const int i = order[e];
@@ -497,7 +500,7 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
     if (kw < 0)
       wq[e] = int(unsigned(q) | (neg ? 0x80000000u : 0u));
     else if (z >= 0)
-      wx[size_t(x + kw) * slots + z * nkw + y + kw] =
+      wx[size_t(x + kt) * slots + z * nkw + y + kt] =
           static_cast<unsigned short>((q + 1) / 2 | (neg ? 0x8000 : 0));
   }
   // coefficients in column order, and the real basis of the virtual ones
@@ -633,8 +636,7 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
   // (with few coefficients the buffer grows to hold them, but not under a
   // workspace cap, where they go through the chi scratch, see order_occupied)
   const size_t psiz_len = (es * size_t(c->no) * nrp + sizeof(double) - 1) / sizeof(double);
-  const bool keep_psiz =
-      psiz_len <= coef_col.size() || !P.workspace_cap || c->no > 2 * c->nh;
+  const bool keep_psiz = psiz_len <= coef_col.size() || !P.workspace_cap;
   double* d_coef = nullptr;
   if ((s = dalloc(c, &d_coef, keep_psiz ? std::max(coef_col.size(), psiz_len) : coef_col.size())))
     return s;
@@ -808,9 +810,8 @@ ltmp2_status block_prepare_t(ltmp2_ctx* c, int itau, int g0, int gb) {
   if (s) return fail(c, s, "transformed-state GEMM launch failed");
   {
     StageTimer tm(c, 4);
-    s = ops->wstates(static_cast<const T*>(c->d_P), c->npw, c->d_wtab, c->sc, gb * c->no,
-                     1.0 / std::sqrt(c->omega), static_cast<T*>(c->d_w), c->nrp,
-                     c->stream);
+    s = ops->wstates(static_cast<const T*>(c->d_P), c->npw, c->d_wtab, c->wtab_k, c->sc, gb * c->no,
+                     1.0 / std::sqrt(c->omega), static_cast<T*>(c->d_w), c->nrp, c->stream);
   }
   if (s) return fail(c, s, "transformed-state launch failed");
   return LTMP2_OK;
@@ -954,7 +955,7 @@ template <class T>
 ltmp2_status hartree_tau_t(ltmp2_ctx* c, int itau) {
   const GridOps<T>* ops = grid_ops<T>(c->n);
   ltmp2_status s;
-  cplx<T>* h = static_cast<cplx<T>*>(c->d_chi);  // free outside the chi route
+  cplx<T>* h = static_cast<cplx<T>*>(c->d_chihat);  // free outside the chi route
   if ((s = order_occupied_t<T>(c))) return s;
   for (int g0 = 0; g0 < c->nh; g0 += c->gblock) {
     const int gb = std::min(c->gblock, c->nh - g0);

@@ -357,7 +357,7 @@ __device__ inline double block_sum(double v, double* red) {
 constexpr int kMaxShells = 8;
 
 struct ShellBins {
-  const signed char* shell = nullptr;  // [n_g] (nullptr: no binning)
+  const signed char* shell = nullptr;  // [n_h] (nullptr: no binning)
   int nb = 0;                          // 1..kMaxShells
   double* out = nullptr;               // [rows][nb] per-row bin sums
 };

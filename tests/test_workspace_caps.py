@@ -1,0 +1,79 @@
+"""The smallest workspace cap that a cell accepts is no larger than the library's
+first footprint: the sum below of the arrays that a context held when its tables
+were one 32-bit word and one byte per plane wave, one FP64 and one packed word
+per auxiliary vector.  Tables of later kernels take the place of these.
+
+Cells of few states and small spheres, whose tables weigh most, up to many
+occupied states against a small auxiliary set; the host library runs against a
+stand-in for the HIP runtime.
+"""
+import pytest
+
+from tests import fake_hip
+
+CODE = r"""
+import itertools, math
+def cell(n, r2, no, nst):
+    k = math.isqrt(r2)
+    r = np.arange(-k, k + 1)
+    m = np.stack([a.ravel() for a in np.meshgrid(r, r, r, indexing="ij")], axis=1)
+    m = m[(m * m).sum(1) <= r2].astype(np.int32)
+    half = [tuple(v) for v in m.tolist() if v > [0, 0, 0]]
+    at = {tuple(v): i for i, v in enumerate(m.tolist())}
+    nst = min(nst, 2 * len(half))
+    if nst <= no:
+        return None
+    c = np.zeros((nst, len(m)), complex)
+    for s in range(nst):
+        v = half[s // 2]
+        c[s, at[v]] = math.sqrt(0.5) * (1j if s % 2 else 1)
+        c[s, at[tuple(-x for x in v)]] = np.conj(c[s, at[v]])
+    e = np.concatenate([np.linspace(-1, -0.5, no), np.linspace(0.5, 2, nst - no)])
+    return m, e, c
+def first_footprint(i, m, prec, nb):
+    up = lambda a, b: (a + b - 1) // b * b
+    es, nt = (8 if prec == 0 else 4), i.n_tau
+    nr, no, nv, nh, ng, npw = up(i.n_r, 128), i.n_occ, i.n_vir, i.n_h, i.n_g, i.n_pw
+    nst, pairs = no + nv, no * (no + 1) // 2
+    ncol = len({tuple(v[1:]) for v in m.tolist()})
+    b = 4 * (2 * ncol + 1) + 9 * npw + 12 * ng + 4 * pairs + 8 * nt * nst
+    b += es * nv * up(npw, 4) + 16 * nst * npw + es * nst * nr + 2 * es * nv * nh * no
+    b += es * nr * nr + 2 * es * nh * nr + 8 * nh * (2 + pairs) + 8 * (2 * nt + 8)
+    if prec == 2:
+        b += 4 * (up(no, 64) + up(nv, 64)) * nr
+        b += 4 * up(nv, 64) * (up(2 * nh * no, 128) + 128 + up(npw, 128))
+    if nb:
+        b += ng + 8 * nh * nb * (2 + pairs) + 16 * nt * nb
+    return b + 2 * es * no * (npw + nr)
+for n, r2, ra, (no, nst), nb in itertools.product((12, 16, 18, 25), (1, 3, 4, 9, 15, 25, 35),
+                                                  (1, 4, 9, 36, 64), ((1, 3), (40, 90)), (0, 4)):
+    if 2 * math.isqrt(r2) >= n or 2 * math.isqrt(ra) >= n or (no > 1 and nb) or \
+            not cell(n, r2, no, nst):
+        continue
+    m, e, c = cell(n, r2, no, nst)
+    side = 0.5 * n
+    hb2 = 0.5 * (2 * math.pi / side) ** 2
+    def make(cap):
+        return L.Context(side, n, hb2 * (r2 + 0.5), hb2 * (ra + 0.25), m, e, c, no, 1,
+                         tau=np.array([1.0]), w=np.array([1.0]), prec={prec}, n_extrap=nb,
+                         workspace_cap=cap)
+    try:
+        with make(0) as ctx:
+            cap = first_footprint(ctx.info, m, {prec}, nb)
+    except L.LTMP2Error:
+        continue                   # the cell's own grid is too small for the auxiliary set
+    try:
+        with make(cap) as ctx:
+            ok = ctx.info.device_bytes <= cap
+    except L.LTMP2Error:
+        ok = False
+    print(json.dumps([n, r2, ra, no, nb, ok]))
+"""
+
+
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_first_footprint_is_accepted(tmp_path, prec):
+    _, cells = fake_hip.run(fake_hip.build(tmp_path), tmp_path, CODE.replace("{prec}", str(prec)),
+                            timeout=300)
+    assert len(cells) > 100
+    assert [c for c in cells if not c[-1]] == []
