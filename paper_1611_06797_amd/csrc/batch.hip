@@ -223,6 +223,7 @@ extern "C" ltmp2_status ltmp2_batch_create(int n_cells, const ltmp2_params* para
     c->prm = params[k];
     c->stream = b->stream;
     c->own_scratch = false;
+    c->batched = true;
     if (mlp_weights) c->mlp_path = mlp_weights;
     b->cells.push_back(c);
     ltmp2_status s = setup_cell(c, miller[k], eps[k], cuse[k], tau ? tau[k] : nullptr,
@@ -282,20 +283,6 @@ extern "C" ltmp2_status ltmp2_batch_create(int n_cells, const ltmp2_params* para
       c->d_chihat = b->chihat;
       c->d_P = b->P;
       c->d_w = static_cast<char*>(b->wpool) + off;
-      if (!c->d_psiz) {  // all cells of a fused launch need theirs at once
-        if (!(s = balloc(b, &c->d_psiz, es * size_t(c->no) * c->nrp)))
-          s = b->prec == LTMP2_FP64
-                  ? grid_ops<double>(c->n)->plane_order(static_cast<const double*>(c->d_psi),
-                                                        c->nrp, c->no,
-                                                        static_cast<double*>(c->d_psiz), b->stream)
-                  : grid_ops<float>(c->n)->plane_order(static_cast<const float*>(c->d_psi), c->nrp,
-                                                       c->no, static_cast<float*>(c->d_psiz),
-                                                       b->stream);
-        if (s) {
-          ltmp2_batch_destroy(b);
-          return bfail(nullptr, s, "orbital reordering failed");
-        }
-      }
       off += 2 * es * size_t(c->gblock) * c->no * c->nrp;
     }
     g.sched.assign(g.max_ntau, std::vector<Round>(g.rounds));

@@ -60,7 +60,8 @@ class Beside {
 };
 
 struct ltmp2_ctx {
-  bool own_scratch = true;  // false: chi / chihat / P / w belong to a batch
+  bool own_scratch = true;  // false: chi / chihat / P / w belong to a batch or spin channel 1
+  bool batched = false;     // cell of a batch
   ltmp2_params prm{};
   std::string err;
   bool failed = false;

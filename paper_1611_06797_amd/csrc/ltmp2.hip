@@ -634,9 +634,11 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
   // the coefficients are needed until the orbitals are on the grid; their
   // memory then holds the occupied orbitals in the pair transforms' order
   // (with few coefficients the buffer grows to hold them, but not under a
-  // workspace cap, where they go through the chi scratch, see order_occupied)
+  // workspace cap, where they go through the chi scratch, see order_occupied;
+  // the cells of a batch need theirs at once, in the room that their caps have
+  // for the transformed states, which the batch pools)
   const size_t psiz_len = (es * size_t(c->no) * nrp + sizeof(double) - 1) / sizeof(double);
-  const bool keep_psiz = psiz_len <= coef_col.size() || !P.workspace_cap;
+  const bool keep_psiz = psiz_len <= coef_col.size() || !P.workspace_cap || c->batched;
   double* d_coef = nullptr;
   if ((s = dalloc(c, &d_coef, keep_psiz ? std::max(coef_col.size(), psiz_len) : coef_col.size())))
     return s;
