@@ -285,7 +285,11 @@ ltmp2_status ltmp2_exchange(ltmp2_ctx* ctx, int itau, int g_first, int g_count,
  * E_x = sum_n w_n E_x(tau_n) (Eqs. dLTMP2Compact and xLTMP2Compact at q = 0),
  * summed in FP64 (Ha per cell).  per_tau (may be NULL) receives [2 n_tau]
  * unweighted values (E_d(tau_n), E_x(tau_n)) pairs; quad_err (may be NULL)
- * the certified max relative error of the quadrature.
+ * the certified max relative error of the quadrature.  The direct terms run on a
+ * second stream of the context beside the exchange terms on hip_stream, which
+ * waits for them.  Everything runs on hip_stream if it has another priority
+ * than the default or a CU mask, while stage times are taken, and in capped
+ * contexts whose occupied orbitals share the chi scratch.
  */
 ltmp2_status ltmp2_energy(ltmp2_ctx* ctx, double* e_direct, double* e_exchange,
                           double* per_tau, double* quad_err);
@@ -431,7 +435,8 @@ const char* ltmp2_mlp_last_error(void);
  * afterwards.
  * Per-cell arrays are as in ltmp2_setup; tau / w may be NULL (or hold NULL
  * entries for cells without a given quadrature).  All cells must use the same
- * precision.  If hip_stream is NULL the batch creates its own stream.
+ * precision.  If hip_stream is NULL the batch creates its own stream; a stream
+ * with another priority than the default or a CU mask runs everything by itself.
  */
 typedef struct ltmp2_batch ltmp2_batch;
 

@@ -215,7 +215,7 @@ extern "C" ltmp2_status ltmp2_batch_create(int n_cells, const ltmp2_params* para
     }
     b->own_stream = true;
   }
-  b->side.create();
+  b->side.create(b->stream);
   b->prec = prec;
   // per-cell preparation without private scratch
   for (int k = 0; k < n_cells; ++k) {

@@ -3,6 +3,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <cstdint>
 #include <string>
 #include <vector>
 
@@ -18,14 +19,30 @@
 struct SideStream {
   hipStream_t st = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
-  // without it (creation failed) everything runs on the caller's stream
-  void create() {
-    if (hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess &&
+  // Without it everything runs on the caller's stream `main`: where creation
+  // failed, and where `main` has a priority or CUs of its own, which the caller
+  // chose for all of the work (and streams of different priorities must not
+  // wait for each other).
+  void create(hipStream_t main) {
+    const bool handle = main && main != hipStreamLegacy && main != hipStreamPerThread;
+    int priority = 0;
+    if ((!handle || (hipStreamGetPriority(main, &priority) == hipSuccess && priority == 0)) &&
+        hipStreamCreateWithFlags(&st, hipStreamNonBlocking) == hipSuccess &&
+        (!handle || same_cus(main, st)) &&
         hipEventCreateWithFlags(&fork, hipEventDisableTiming) == hipSuccess &&
         hipEventCreateWithFlags(&join, hipEventDisableTiming) == hipSuccess)
       return;
     (void)hipGetLastError();
     destroy();
+  }
+  static bool same_cus(hipStream_t a, hipStream_t b) {
+    uint32_t ma[32] = {}, mb[32] = {};
+    if (hipExtStreamGetCUMask(a, 32, ma) != hipSuccess ||
+        hipExtStreamGetCUMask(b, 32, mb) != hipSuccess)
+      return false;
+    for (int k = 0; k < 32; ++k)
+      if (ma[k] != mb[k]) return false;
+    return true;
   }
   void destroy() {
     if (join) (void)hipEventDestroy(join);

@@ -678,7 +678,7 @@ ltmp2_status setup_impl(ltmp2_ctx* c, const int32_t* miller, const double* eps,
   }
   // transformed-state buffers last, sized by what the cap leaves
   if (c->own_scratch) {
-    c->side.create();
+    c->side.create(c->stream);
     if (P.workspace_cap) {
       if (c->bytes + per_g > P.workspace_cap)
         return fail(nullptr, LTMP2_ENOMEM, "device footprint exceeds the workspace cap");
