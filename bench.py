@@ -35,10 +35,11 @@ PEAK_FP32 = 157.3e12     # FP32 vector and matrix, FLOP/s
 PEAK_BF16 = 2.5e15       # BF16 dense matrix, FLOP/s
 PEAK_HBM = 8.0e12        # bytes/s
 
-# Sources of the pair-transform kernel (device code and its launch shapes);
-# HBM traffic figures taken with rocprofv3 counters are only reported while
-# these are unchanged.
-PAIR_SOURCES = ("fft.hpp", "rfft.hpp", "kernels_pair.hpp", "grid_kernels.hip")
+# Sources of the pair-transform kernel (device code, launch shapes, order of the
+# pairs and G' block size); HBM traffic figures taken with rocprofv3 counters are
+# only reported while these are unchanged.
+PAIR_SOURCES = ("fft.hpp", "rfft.hpp", "transforms.hpp", "launch_items.hpp", "kernels_pair.hpp",
+                "grid_kernels.hip", "ltmp2.hip")
 COPY_PROBE_BYTES = 1 << 30
 
 
