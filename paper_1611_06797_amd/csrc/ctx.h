@@ -173,8 +173,7 @@ struct ltmp2_ctx {
 namespace ltmp2 {
 // Host drivers of one Laplace point (ltmp2.hip); values land in d_scal.
 ltmp2_status run_direct(ltmp2_ctx* c, int itau, hipStream_t st);
-ltmp2_status run_exchange(ltmp2_ctx* c, int itau, int g_first, int g_count);
-// Pieces of run_exchange used by batched execution.
+// Pieces of the exchange term used by batched execution.
 PairCell pair_cell(const ltmp2_ctx* c, int g0, int gb);
 // Occupied orbitals in the pair transforms' order: kept, or in the chi scratch.
 inline void* occupied(const ltmp2_ctx* c) { return c->d_psiz ? c->d_psiz : c->d_chi; }

@@ -28,9 +28,9 @@ __global__ __launch_bounds__(kThreads) void k_orbitals(const cplx<double>* __res
   const long p = blockIdx.x;
   const cplx<double>* c = coef + p * npw;
   T* out = psi + p * ld;
-  auto cf = [&](int, int e) { return cplx<T>{T(c[e].x), T(c[e].y)}; };
-  auto st = [&](int, int x, int y, int z, cplx<T> v) { out[(x * N + z) * N + y] = T(scale) * v.x; };
-  inverse_sphere<T, N, 1>(cf, st, 1, sc.kmax, sx, sc.ncol, sc.cdesc, sc.cstart, sc.ckx, L);
+  auto cf = [&](int e) { return cplx<T>{T(c[e].x), T(c[e].y)}; };
+  auto st = [&](int x, int y, int z, cplx<T> v) { out[(x * N + z) * N + y] = T(scale) * v.x; };
+  inverse_sphere<T, N>(cf, st, sc.kmax, sx, sc.ncol, sc.cdesc, sc.cstart, sc.ckx, L);
 }
 
 // ---------------------------------------------------------------------------
@@ -58,16 +58,16 @@ __global__ __launch_bounds__(kThreads) void k_chi_cols(const cplx<T>* __restrict
   const int g = blockIdx.x;
   const cplx<T>* col = chihat + long(g) * ld;
   int gd[OPT];
-  cplx<T> acc[1][OPT];
+  cplx<T> acc[OPT];
 #pragma unroll
   for (int t = 0; t < OPT; ++t) {
     const int o = threadIdx.x + t * kThreads;
     gd[t] = (o < ng) ? gdesc_all[o] : 0;
-    acc[0][t] = {T(0), T(0)};
+    acc[t] = {T(0), T(0)};
   }
   __syncthreads();
-  auto ld_ = [&](int, int x, int y, int z) { return col[(x * N + z) * N + y]; };
-  forward_pruned<T, -1, N, 1, OPT>(ld_, 1, kmax, sx, gd, ng, acc, L);
+  auto ld_ = [&](int x, int y, int z) { return col[(x * N + z) * N + y]; };
+  forward_pruned<T, -1, N, OPT>(ld_, kmax, sx, gd, ng, acc, L);
   double s = 0.0;
   double sb[kMaxShells] = {};
   const int sg = bins.shell ? bins.shell[g] : 0;
@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kThreads) void k_chi_cols(const cplx<T>* __restrict
   for (int t = 0; t < OPT; ++t) {
     const int o = threadIdx.x + t * kThreads;
     if (o < ng) {
-      const double re = dV * double(acc[0][t].x), im = dV * double(acc[0][t].y);
+      const double re = dV * double(acc[t].x), im = dV * double(acc[t].y);
       const int oh = o < nh ? o : o - nh;
       const double term = v[oh] * (re * re + im * im);
       s += term;
@@ -137,22 +137,22 @@ __global__ __launch_bounds__(kThreads) void k_hartree(const cplx<T>* __restrict_
   const int gl = blockIdx.x;
   const cplx<T>* col = h + long(gl) * ld;
   int gd[OPT];
-  cplx<T> acc[1][OPT];
+  cplx<T> acc[OPT];
 #pragma unroll
   for (int t = 0; t < OPT; ++t) {
     const int o = threadIdx.x + t * kThreads;
     gd[t] = (o < ng) ? gdesc_all[o] : 0;
-    acc[0][t] = {T(0), T(0)};
+    acc[t] = {T(0), T(0)};
   }
   __syncthreads();
-  auto ld_ = [&](int, int x, int y, int z) { return col[(z * N + x) * N + y]; };
-  forward_pruned<T, -1, N, 1, OPT>(ld_, 1, kmax, sx, gd, ng, acc, L);
+  auto ld_ = [&](int x, int y, int z) { return col[(z * N + x) * N + y]; };
+  forward_pruned<T, -1, N, OPT>(ld_, kmax, sx, gd, ng, acc, L);
   double s = 0.0;
 #pragma unroll
   for (int t = 0; t < OPT; ++t) {
     const int o = threadIdx.x + t * kThreads;
     if (o < ng) {
-      const double re = dV * double(acc[0][t].x), im = dV * double(acc[0][t].y);
+      const double re = dV * double(acc[t].x), im = dV * double(acc[t].y);
       s += v[o < ng / 2 ? o : o - ng / 2] * (re * re + im * im);
     }
   }
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(kThreads) void k_wstates(const T* __restrict__ P, i
   T* out = w + 2 * item * ld;
   // W_j(G) of sphere entry e, gathered from the real basis (each entry is
   // used once per slab group)
-  auto cf = [&](int, int e) {
+  auto cf = [&](int e) {
     const int q = wq[e] & 0xffff;
     T re = pre[q], im = pim[q];
     if (q > 0) {
@@ -194,12 +194,12 @@ __global__ __launch_bounds__(kThreads) void k_wstates(const T* __restrict__ P, i
     }
     return cplx<T>{re, im};
   };
-  auto st = [&](int, int x, int y, int z, cplx<T> v) {
+  auto st = [&](int x, int y, int z, cplx<T> v) {
     T* o = out + (z * N + x) * N + y;
     o[0] = T(scale) * v.x;
     o[ld] = T(scale) * v.y;
   };
-  inverse_sphere<T, N, 1>(cf, st, 1, sc.kmax, sx, sc.ncol, sc.cdesc, sc.cstart, sc.ckx, L);
+  inverse_sphere<T, N>(cf, st, sc.kmax, sx, sc.ncol, sc.cdesc, sc.cstart, sc.ckx, L);
 }
 
 }  // namespace ltmp2

@@ -29,17 +29,6 @@ namespace {
 
 thread_local std::string g_setup_error;
 
-struct DevBuf {
-  void* p = nullptr;
-  size_t bytes = 0;
-};
-
-}  // namespace
-
-
-
-namespace {
-
 ltmp2_status fail(ltmp2_ctx* c, ltmp2_status s, const std::string& msg) {
   if (c) {
     c->err = msg;
@@ -1009,9 +998,6 @@ ltmp2_status run_direct(ltmp2_ctx* c, int itau, hipStream_t st) {
   c->stream = own;
   if (c->beta) c->beta->stream = own;
   return s;
-}
-ltmp2_status run_exchange(ltmp2_ctx* c, int itau, int g_first, int g_count) {
-  return exchange_tau(c, itau, g_first, g_count);
 }
 ltmp2_status exchange_block_prepare(ltmp2_ctx* c, int itau, int g0, int gb) {
   return block_prepare(c, itau, g0, gb);

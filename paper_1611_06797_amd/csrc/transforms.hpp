@@ -115,41 +115,14 @@ __host__ __device__ constexpr int slab_tile_at_most(int n, int cap) {
   return 1;
 }
 
-// In-place length-D transforms of the nc columns of a [D][nc] LDS array.
-template <class T, int S, int D, int NT = kThreads>
-__device__ inline void column_fft(cplx<T>* a, int nc) {
-  for (int c = threadIdx.x; c < nc; c += NT) {
-    cplx<T> v[D];
-#pragma unroll
-    for (int k = 0; k < D; ++k) v[k] = a[k * nc + c];
-    Fft<T, S, D>::run(v);
-#pragma unroll
-    for (int k = 0; k < D; ++k) a[k * nc + c] = v[k];
-  }
-}
-
-// Slab tiles: divisors d <= 12 of the grid size (d = 1 is a no-op).
-template <class T, int S, int N, int NT = kThreads>
-__device__ inline void column_fft_tile(cplx<T>* a, int d, int nc) {
-  if constexpr (N % 12 == 0) if (d == 12) return column_fft<T, S, 12, NT>(a, nc);
-  if constexpr (N % 10 == 0) if (d == 10) return column_fft<T, S, 10, NT>(a, nc);
-  if constexpr (N % 9 == 0) if (d == 9) return column_fft<T, S, 9, NT>(a, nc);
-  if constexpr (N % 8 == 0) if (d == 8) return column_fft<T, S, 8, NT>(a, nc);
-  if constexpr (N % 6 == 0) if (d == 6) return column_fft<T, S, 6, NT>(a, nc);
-  if constexpr (N % 5 == 0) if (d == 5) return column_fft<T, S, 5, NT>(a, nc);
-  if constexpr (N % 4 == 0) if (d == 4) return column_fft<T, S, 4, NT>(a, nc);
-  if constexpr (N % 3 == 0) if (d == 3) return column_fft<T, S, 3, NT>(a, nc);
-  if constexpr (N % 2 == 0) if (d == 2) return column_fft<T, S, 2, NT>(a, nc);
-}
-
 // Length-D transforms across the planes of the forward layout: column
 // (kzi, kyi) of plane xs sits at a[xs * pstride + kzi * R + kyi].
-template <class T, int S, int D, int NT>
+template <class T, int S, int D>
 __device__ inline void column_fft_rows(cplx<T>* a, int nk, int R, int pstride) {
   // c / nk by a multiply-high: exact for c < nk^2 <= 2^12 (the error of the
   // rounded-up reciprocal stays below 2^32 / c)
   const unsigned inv = 0xffffffffu / unsigned(nk) + 1u;
-  for (int c = threadIdx.x; c < nk * nk; c += NT) {
+  for (int c = threadIdx.x; c < nk * nk; c += kThreads) {
     const int kzi = int(__umulhi(unsigned(c), inv)), kyi = c - kzi * nk;
     cplx<T>* b = a + kzi * R + kyi;
     cplx<T> v[D];
@@ -161,37 +134,34 @@ __device__ inline void column_fft_rows(cplx<T>* a, int nk, int R, int pstride) {
   }
 }
 
-template <class T, int S, int N, int NT = kThreads>
+template <class T, int S, int N>
 __device__ inline void column_fft_rows_tile(cplx<T>* a, int d, int nk, int R, int pstride) {
-  if constexpr (N % 12 == 0) if (d == 12) return column_fft_rows<T, S, 12, NT>(a, nk, R, pstride);
-  if constexpr (N % 10 == 0) if (d == 10) return column_fft_rows<T, S, 10, NT>(a, nk, R, pstride);
-  if constexpr (N % 9 == 0) if (d == 9) return column_fft_rows<T, S, 9, NT>(a, nk, R, pstride);
-  if constexpr (N % 8 == 0) if (d == 8) return column_fft_rows<T, S, 8, NT>(a, nk, R, pstride);
-  if constexpr (N % 6 == 0) if (d == 6) return column_fft_rows<T, S, 6, NT>(a, nk, R, pstride);
-  if constexpr (N % 5 == 0) if (d == 5) return column_fft_rows<T, S, 5, NT>(a, nk, R, pstride);
-  if constexpr (N % 4 == 0) if (d == 4) return column_fft_rows<T, S, 4, NT>(a, nk, R, pstride);
-  if constexpr (N % 3 == 0) if (d == 3) return column_fft_rows<T, S, 3, NT>(a, nk, R, pstride);
-  if constexpr (N % 2 == 0) if (d == 2) return column_fft_rows<T, S, 2, NT>(a, nk, R, pstride);
+  if constexpr (N % 12 == 0) if (d == 12) return column_fft_rows<T, S, 12>(a, nk, R, pstride);
+  if constexpr (N % 10 == 0) if (d == 10) return column_fft_rows<T, S, 10>(a, nk, R, pstride);
+  if constexpr (N % 9 == 0) if (d == 9) return column_fft_rows<T, S, 9>(a, nk, R, pstride);
+  if constexpr (N % 8 == 0) if (d == 8) return column_fft_rows<T, S, 8>(a, nk, R, pstride);
+  if constexpr (N % 6 == 0) if (d == 6) return column_fft_rows<T, S, 6>(a, nk, R, pstride);
+  if constexpr (N % 5 == 0) if (d == 5) return column_fft_rows<T, S, 5>(a, nk, R, pstride);
+  if constexpr (N % 4 == 0) if (d == 4) return column_fft_rows<T, S, 4>(a, nk, R, pstride);
+  if constexpr (N % 3 == 0) if (d == 3) return column_fft_rows<T, S, 3>(a, nk, R, pstride);
+  if constexpr (N % 2 == 0) if (d == 2) return column_fft_rows<T, S, 2>(a, nk, R, pstride);
 }
 
-// Forward pruned transform of NF fields.  Load(f, x, y, z) returns the
-// field value; acc[f][t] accumulates output o = threadIdx.x + t * NT
-// (o < nout; NT threads per workgroup) whose packed descriptor is gdesc[t]
-// (pre-loaded by the caller).
+// Forward pruned transform of a field.  Load(x, y, z) returns the field value;
+// acc[t] accumulates output o = threadIdx.x + t * kThreads (o < nout) whose
+// packed descriptor is gdesc[t] (pre-loaded by the caller).
 //
 // The x transform is split as N = M * sx (sx divides N): slab group x2
 // holds the planes x = x2 + M xs, xs < sx.  After the z and y passes of the
 // group, a length-sx FFT across its planes gives, for every kept (ky, kz),
 // Y_x2(q) = sum_xs f(x2 + M xs) w_sx^{q xs}; output kx then needs only
 // w_N^{kx x2} Y_x2(kx mod sx), one product per group instead of sx.
-// KM >= 0 fixes kmax = KM at compile time (see kwin).  L is the forward
-// layout (fwd_lds).
-template <class T, int S, int N, int NF, int OPT, int NT = kThreads, int KM = -1, class Load>
-__device__ __forceinline__ void forward_pruned(const Load& ld, int nf_active, int kmax_rt, int sx,
+// L is the forward layout (fwd_lds).
+template <class T, int S, int N, int OPT, class Load>
+__device__ __forceinline__ void forward_pruned(const Load& ld, int kmax, int sx,
                                                const int (&gdesc)[OPT], int nout,
-                                               cplx<T> (&acc)[NF][OPT], const SlabLds<T>& L) {
+                                               cplx<T> (&acc)[OPT], const SlabLds<T>& L) {
   constexpr int R = slab_row(N);
-  const int kmax = KM >= 0 ? KM : kmax_rt;
   const int nk = 2 * kmax + 1, M = N / sx, pstride = nk * R;
   const int tid = threadIdx.x;
   // per output: offset of its (residue plane, kz, ky) entry (low 24 bits) and kx
@@ -202,68 +172,62 @@ __device__ __forceinline__ void forward_pruned(const Load& ld, int nf_active, in
     ox[t] = ((kxm % sx) * pstride + kzi * R + kyi) | (kxm << 24);
   }
   for (int x2 = 0; x2 < M; ++x2) {
+    // z pass: line (xs, y) -> rows (xs, kz)
+    for (int l = tid; l < sx * N; l += kThreads) {
+      const int xs = l / N, y = l - xs * N, x = x2 + M * xs;
+      cplx<T> v[N];
 #pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      if (f >= nf_active) break;
-      // z pass: line (xs, y) -> rows (xs, kz)
-      for (int l = tid; l < sx * N; l += NT) {
-        const int xs = l / N, y = l - xs * N, x = x2 + M * xs;
-        cplx<T> v[N];
+      for (int z = 0; z < N; ++z) v[z] = ld(x, y, z);
+      Fft<T, S, N>::run(v);
 #pragma unroll
-        for (int z = 0; z < N; ++z) v[z] = ld(f, x, y, z);
-        Fft<T, S, N>::run(v);
-#pragma unroll
-        for (int z = 0; z < N; ++z) {
-          const int kz = (z <= N / 2) ? z : z - N;
-          if (kz >= -kmax && kz <= kmax) L.t1[(xs * nk + kz + kmax) * R + y] = v[z];
-        }
+      for (int z = 0; z < N; ++z) {
+        const int kz = (z <= N / 2) ? z : z - N;
+        if (kz >= -kmax && kz <= kmax) L.t1[(xs * nk + kz + kmax) * R + y] = v[z];
       }
-      __syncthreads();
-      // y pass: row (xs, kz) in place; the kept ky land at the row's start
-      for (int l = tid; l < sx * nk; l += NT) {
-        cplx<T>* row = L.t1 + l * R;
-        cplx<T> v[N];
-#pragma unroll
-        for (int y = 0; y < N; ++y) v[y] = row[y];
-        Fft<T, S, N>::run(v);
-#pragma unroll
-        for (int y = 0; y < N; ++y) {
-          const int ky = (y <= N / 2) ? y : y - N;
-          if (ky >= -kmax && ky <= kmax) row[ky + kmax] = v[y];
-        }
-      }
-      __syncthreads();
-      // x: length-sx FFT across the group's planes, then one product per output
-      column_fft_rows_tile<T, S, N, NT>(L.t1, sx, nk, R, pstride);
-      if (sx > 1) __syncthreads();
-#pragma unroll
-      for (int t = 0; t < OPT; ++t) {
-        const int o = tid + t * NT;
-        if (o < nout)
-          acc[f][t] = cfma(L.tw[((ox[t] >> 24) * x2) % N], L.t1[ox[t] & 0xffffff], acc[f][t]);
-      }
-      __syncthreads();  // the next z pass overwrites the rows
     }
+    __syncthreads();
+    // y pass: row (xs, kz) in place; the kept ky land at the row's start
+    for (int l = tid; l < sx * nk; l += kThreads) {
+      cplx<T>* row = L.t1 + l * R;
+      cplx<T> v[N];
+#pragma unroll
+      for (int y = 0; y < N; ++y) v[y] = row[y];
+      Fft<T, S, N>::run(v);
+#pragma unroll
+      for (int y = 0; y < N; ++y) {
+        const int ky = (y <= N / 2) ? y : y - N;
+        if (ky >= -kmax && ky <= kmax) row[ky + kmax] = v[y];
+      }
+    }
+    __syncthreads();
+    // x: length-sx FFT across the group's planes, then one product per output
+    column_fft_rows_tile<T, S, N>(L.t1, sx, nk, R, pstride);
+    if (sx > 1) __syncthreads();
+#pragma unroll
+    for (int t = 0; t < OPT; ++t) {
+      const int o = tid + t * kThreads;
+      if (o < nout) acc[t] = cfma(L.tw[((ox[t] >> 24) * x2) % N], L.t1[ox[t] & 0xffffff], acc[t]);
+    }
+    __syncthreads();  // the next z pass overwrites the rows
   }
 }
 
-// Inverse transform of NF coefficient vectors given on a sphere whose
-// entries are grouped in (ky, kz) columns: column c covers entries
-// [cstart[c], cstart[c+1]) with packed (ky + kmax) | (kz + kmax) << 8 in
-// cdesc[c] and consecutive, ascending kx values ckx[e].  Coef(f, e) returns
-// entry e of item f; Store(f, x, y, z, v) receives the synthesised grid
-// value.  L is the inverse layout (inv_lds) with its twiddles filled; the
-// first barrier inside orders them before their use.  Requires fewer than
-// 2^16 entries, and column lengths and N below 64.
+// Inverse transform of coefficients given on a sphere whose entries are grouped
+// in (ky, kz) columns: column c covers entries [cstart[c], cstart[c+1]) with
+// packed (ky + kmax) | (kz + kmax) << 8 in cdesc[c] and consecutive, ascending kx
+// values ckx[e].  Coef(e) returns entry e; Store(x, y, z, v) receives the
+// synthesised grid value.  L is the inverse layout (inv_lds) with its twiddles
+// filled; the first barrier inside orders them before their use.  Requires fewer
+// than 2^16 entries, and column lengths and N below 64.
 //
 // The x transform uses the same split as the forward one (sx divides N,
 // group x2 = planes x2 + M xs): per (ky, kz) slot and residue q < sx,
 // Z(q) = sum_{kx = q mod sx} c(kx) w_N^{kx x2} (zero for slots outside the
 // sphere), then a length-sx FFT over q gives the group's planes.
-template <class T, int N, int NF, class Coef, class Store>
-__device__ inline void inverse_sphere(const Coef& cf, const Store& st, int nf_active,
-                                      int kmax, int sx, int ncol, const int* cdesc,
-                                      const int* cstart, const int* ckx, const SlabLds<T>& L) {
+template <class T, int N, class Coef, class Store>
+__device__ inline void inverse_sphere(const Coef& cf, const Store& st, int kmax, int sx, int ncol,
+                                      const int* cdesc, const int* cstart, const int* ckx,
+                                      const SlabLds<T>& L) {
   constexpr int R = slab_row(N);
   const int nk = 2 * kmax + 1, nc = nk * nk, M = N / sx;
   const int tid = threadIdx.x;
@@ -277,60 +241,56 @@ __device__ inline void inverse_sphere(const Coef& cf, const Store& st, int nf_ac
   }
   __syncthreads();
   for (int x2 = 0; x2 < M; ++x2) {
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-      if (f >= nf_active) break;
-      // x stage: residue sums for every slot s = kzi * nk + kyi
-      for (int l = tid; l < sx * nc; l += kThreads) {
-        const int q = l / nc, sl = l - q * nc;
-        const int m = L.cmap[sl];
-        cplx<T> s = {T(0), T(0)};
-        if (m != 0) {
-          const int e0 = m & 0xffff, e1 = e0 + ((m >> 16) & 63);
-          int kxm = (m >> 22) & 63;
-          const int skip = (q - kxm % sx + sx) % sx;
-          kxm += skip;
-          for (int e = e0 + skip; e < e1; e += sx) {
-            s = cfma(cf(f, e), L.tw[(kxm * x2) % N], s);
-            kxm += sx;
-          }
+    // x stage: residue sums for every slot s = kzi * nk + kyi
+    for (int l = tid; l < sx * nc; l += kThreads) {
+      const int q = l / nc, sl = l - q * nc;
+      const int m = L.cmap[sl];
+      cplx<T> s = {T(0), T(0)};
+      if (m != 0) {
+        const int e0 = m & 0xffff, e1 = e0 + ((m >> 16) & 63);
+        int kxm = (m >> 22) & 63;
+        const int skip = (q - kxm % sx + sx) % sx;
+        kxm += skip;
+        for (int e = e0 + skip; e < e1; e += sx) {
+          s = cfma(cf(e), L.tw[(kxm * x2) % N], s);
+          kxm += sx;
         }
-        const int kzi = sl / nk;
-        L.t1[(q * nk + kzi) * R + (sl - kzi * nk)] = s;
       }
-      __syncthreads();
-      column_fft_rows_tile<T, 1, N>(L.t1, sx, nk, R, nk * R);
-      if (sx > 1) __syncthreads();
-      // y stage: line (xs, kz), expanded in place from nk to N values
-      for (int l = tid; l < sx * nk; l += kThreads) {
-        cplx<T>* row = L.t1 + l * R;
-        cplx<T> v[N];
-#pragma unroll
-        for (int y = 0; y < N; ++y) {
-          const int ky = (y <= N / 2) ? y : y - N;
-          v[y] = (ky >= -kmax && ky <= kmax) ? row[ky + kmax] : cplx<T>{T(0), T(0)};
-        }
-        Fft<T, 1, N>::run(v);
-#pragma unroll
-        for (int y = 0; y < N; ++y) row[y] = v[y];
-      }
-      __syncthreads();
-      // z stage: line (xs, y)
-      for (int l = tid; l < sx * N; l += kThreads) {
-        const int xs = l / N, y = l - xs * N, x = x2 + M * xs;
-        cplx<T> v[N];
-#pragma unroll
-        for (int z = 0; z < N; ++z) {
-          const int kz = (z <= N / 2) ? z : z - N;
-          v[z] = (kz >= -kmax && kz <= kmax) ? L.t1[(xs * nk + kz + kmax) * R + y]
-                                             : cplx<T>{T(0), T(0)};
-        }
-        Fft<T, 1, N>::run(v);
-#pragma unroll
-        for (int z = 0; z < N; ++z) st(f, x, y, z, v[z]);
-      }
-      __syncthreads();  // the next x stage overwrites the rows
+      const int kzi = sl / nk;
+      L.t1[(q * nk + kzi) * R + (sl - kzi * nk)] = s;
     }
+    __syncthreads();
+    column_fft_rows_tile<T, 1, N>(L.t1, sx, nk, R, nk * R);
+    if (sx > 1) __syncthreads();
+    // y stage: line (xs, kz), expanded in place from nk to N values
+    for (int l = tid; l < sx * nk; l += kThreads) {
+      cplx<T>* row = L.t1 + l * R;
+      cplx<T> v[N];
+#pragma unroll
+      for (int y = 0; y < N; ++y) {
+        const int ky = (y <= N / 2) ? y : y - N;
+        v[y] = (ky >= -kmax && ky <= kmax) ? row[ky + kmax] : cplx<T>{T(0), T(0)};
+      }
+      Fft<T, 1, N>::run(v);
+#pragma unroll
+      for (int y = 0; y < N; ++y) row[y] = v[y];
+    }
+    __syncthreads();
+    // z stage: line (xs, y)
+    for (int l = tid; l < sx * N; l += kThreads) {
+      const int xs = l / N, y = l - xs * N, x = x2 + M * xs;
+      cplx<T> v[N];
+#pragma unroll
+      for (int z = 0; z < N; ++z) {
+        const int kz = (z <= N / 2) ? z : z - N;
+        v[z] = (kz >= -kmax && kz <= kmax) ? L.t1[(xs * nk + kz + kmax) * R + y]
+                                           : cplx<T>{T(0), T(0)};
+      }
+      Fft<T, 1, N>::run(v);
+#pragma unroll
+      for (int z = 0; z < N; ++z) st(x, y, z, v[z]);
+    }
+    __syncthreads();  // the next x stage overwrites the rows
   }
 }
 
