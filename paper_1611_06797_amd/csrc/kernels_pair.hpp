@@ -28,10 +28,14 @@
 // overlap them, so the work is cut into small workgroups, as many per CU as
 // shared memory holds, with as few barriers per field as possible.  Complex
 // lines in 256-thread workgroups against this form, ns per item (one G', one
-// pair) in FP32: 12 grid 4.5 -> 2.4, 15: 10.2 -> 4.8, 18: 13.2 -> 8.7, 20:
-// 21.9 -> 11.3, 24: 31.0 -> 19.6, 27: 51.4 -> 35.7, 30: 88.5 -> 49, 36:
-// 112 -> 94; in FP64, 15: 19.4 -> 13.4, 20: 56 -> 38, 24: 77 -> 68, 27:
-// 189 -> 112.
+// pair) of launches of 30 000 to 100 000 items: in FP32 12 grid 5.0 -> 3.0, 15:
+// 10.7 -> 5.5, 16: 9.5 -> 6.2, 18: 14.3 -> 10.1, 20: 24.6 -> 14.2, 24: 32 -> 23,
+// 25: 97 -> 35, 27: 85 -> 39, 30: 91 -> 50, 32: 98 -> 62, 36: 112 -> 99, 40: 219
+// -> 136; in FP64 12: 8.9 -> 8.6, 15: 19.6 -> 14.8, 16: 18.6 -> 16.4, 18: 24.7 ->
+// 25.7 (the one grid that did not gain), 20: 42 -> 39, 24: 61 -> 60, 25: 240 ->
+// 99, 27: 196 -> 100, 30: 336 -> 165, 32: 308 -> 199, 36: 516 -> 290, 40: 575 ->
+// 390.  The figures at the rules below are of a stand-alone launch of 31 200
+// items whose transformed states do not fit the caches.
 #pragma once
 #include "launch_items.hpp"
 #include "rfft.hpp"
@@ -98,16 +102,15 @@ __host__ __device__ constexpr size_t pair_lds_bytes(size_t es, int n, int k, int
 }
 
 // Threads per workgroup: at least one per column; beyond that the smallest
-// workgroups that still fill the CU's wave slots from its shared memory
-// (128 against 192 threads on the 18 grid 8.8 and 8.7 ns per item, 192 against
-// 320 on the 24 grid 18.3 and 22.2, 256 against 384 on the 27 grid 36 and 45,
-// 512 against 384 on the 36 grid 94 and 109; the 12 grid would run 64 threads
-// 3 % faster when the card is full, and loses 20 % to latency when it is not).
+// workgroups that still fill the CU's wave slots from its shared memory (ns per
+// item, FP32: 18 grid 192 threads 9.8, 128 10.3; 24 grid, |k| <= 6, 192 threads
+// 20.0, 320 22.1; 27 grid 256 threads 42.6, 384 54; 36 grid 512 threads 108, 384
+// 116; FP64: 18 grid 192 threads 26.9, 128 27.4.  The 12 grid would run 64 threads
+// 5 % faster when the card is full, and loses 20 % to latency when it is not).
 // pair_threads has the last word: workgroups alone on their CU take 512.
-__host__ __device__ constexpr int pair_threads_shared(size_t es, int n, int k) {
+__host__ __device__ constexpr int pair_threads_shared(int n, int k) {
   const int cols = (pair_cols_max(k) + 63) / 64 * 64;
-  int nt = n <= 18 ? 128 : n <= 24 ? 192 : n <= 27 ? 256 : 512;
-  if (es == 8 && n == 18) nt = 192;
+  const int nt = n <= 16 ? 128 : n <= 24 ? 192 : n <= 27 ? 256 : 512;
   return cols > nt ? cols : nt;
 }
 
@@ -127,8 +130,8 @@ __host__ __device__ constexpr int slab_fill(int n, int ns, int nt) {
 }
 
 // Slabs per field.  One where the whole field fits next to a second workgroup
-// (each slab costs two more barriers: 27 grid, FP32, three workgroups per CU
-// of one slab 35.7 ns per item, four of three slabs 37.4), else the fewest
+// (each slab costs two more barriers; a third or fourth workgroup gains nothing
+// in FP32: 27 grid, one slab and three slabs 42.6 ns per item), else the fewest
 // that leave room for two workgroups and whose z lines fill more than 60 % of
 // their rounds (FP64: 25 grid 110 ns in five slabs of 125 lines for 256
 // threads, 101 in one slab; 27 grid, |k| <= 10, nine slabs of 81 lines 346,
@@ -141,7 +144,7 @@ __host__ __device__ constexpr int slab_fill(int n, int ns, int nt) {
 // one workgroup per CU, 170).  On the 32 grid (|k| <= 9, FP32) the exact count
 // lets one slab pass where a rounded one took two (68 -> 63 ns).
 __host__ __device__ constexpr int pair_slabs(size_t es, int n, int k, bool bins = false) {
-  const int nt = pair_threads_shared(es, n, k), cols = pair_cols_max(k);
+  const int nt = pair_threads_shared(n, k), cols = pair_cols_max(k);
   const size_t stat = pair_static(k, nt, bins);
   for (int wgs = es == 8 ? 3 : 2; wgs >= 2; --wgs)
     for (int ns = 1; ns <= n; ++ns)
@@ -158,7 +161,7 @@ __host__ __device__ constexpr int pair_slabs(size_t es, int n, int k, bool bins 
 // allow (FP64: 24 grid, |k| <= 10, 384 threads 95 ns, 512 threads 90; 25 grid 256
 // threads 125, 512 threads 101).
 __host__ __device__ constexpr int pair_threads(size_t es, int n, int k) {
-  const int nt = pair_threads_shared(es, n, k);
+  const int nt = pair_threads_shared(n, k);
   const size_t lds = pair_lds_bytes(es, n, k, pair_slabs(es, n, k), pair_cols_max(k));
   return es == 8 && lds + pair_static(k, nt, false) > size_t(80) * 1024 && nt < 512 ? 512 : nt;
 }
@@ -330,7 +333,8 @@ __device__ __forceinline__ void pair_item(const PairCell& pc, int gl, int p, T* 
   T* t2 = t1 + SP * nk * line_row(N);
   const bool split = BINS && pc.shm2;
   // tables by m^2 in shared memory: read one column at a time in the
-  // epilogue, a chain of dependent global reads otherwise (36 grid 115 -> 94)
+  // epilogue, a chain of dependent global reads otherwise (a fifth of the 36
+  // grid's time)
   for (int k = tid; k < pc.nm2; k += NT) {
     vm[k] = k >= 1 && k <= pc.m2lim ? 4.0 * M_PI / (pc.vden * double(k)) : 0.0;
     if constexpr (BINS)
