@@ -247,9 +247,10 @@ __device__ __forceinline__ void line_transform(const T* pa, const T* pu, const i
       if constexpr (PROD)
 #pragma unroll
         for (int z = 0; z < N; ++z) u[z] = field_load<T>(ru, r0 + unsigned(z * P * sizeof(T)));
-      // all loads of the line are issued before the first product waits (left
-      // to itself the compiler spaces them out: 24 grid, FP32, 37 instead of 25
-      // ns; in FP64 it does not, and 18 to 25 grids are 1 % faster without)
+      // all loads of the line are issued before the first product waits: in FP32
+      // calls on the 24 and 40 grids are 1 to 1.6 % faster with it, chi on the 36
+      // grid 2 % (its exchange 1.6 % slower); in FP64 15 to 25 grids are 1 % faster
+      // without
       if constexpr (sizeof(T) == 4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int z = 0; z < N; ++z) v[z] = PROD ? a[z] * u[z] : a[z];
