@@ -80,8 +80,8 @@ struct WstShape {
 // coefficient pair in a row of P (0: G = 0; (npw + 1) / 2: none, as the last entry
 // says), bit 15 set where its conjugate is meant (sets that fit shared memory
 // have fewer than 2^15 pairs).  kt = K, or the set's own largest index below it
-// (SMALL: contexts under a workspace cap; its range checks take 1 to 7 % of the
-// kernel's time).
+// (SMALL: contexts under a workspace cap; its range checks take 1 to 8 % of the
+// kernel's time, on the 30 grid in FP32 a quarter).
 template <class T, int N, int K, bool WIDE, bool SMALL>
 __global__ __launch_bounds__((WstShape<T, N, K, WIDE>::NT), (WstShape<T, N, K, WIDE>::MINW))
 void k_wstates_real(const T* __restrict__ P, int npw, const unsigned short* __restrict__ wx, int kt,
