@@ -29,7 +29,7 @@
 // shared memory holds, with as few barriers per field as possible.  Complex
 // lines in 256-thread workgroups against this form, ns per item (one G', one
 // pair) of launches of 30 000 to 100 000 items: in FP32 12 grid 5.0 -> 3.0, 15:
-// 10.7 -> 5.5, 16: 9.5 -> 6.2, 18: 14.3 -> 10.1, 20: 24.6 -> 14.2, 24: 32 -> 23,
+// 10.7 -> 5.5, 16: 9.5 -> 6.2, 18: 14.3 -> 10.6, 20: 24.6 -> 14.2, 24: 32 -> 23,
 // 25: 97 -> 35, 27: 85 -> 39, 30: 91 -> 50, 32: 98 -> 62, 36: 112 -> 99, 40: 219
 // -> 136; in FP64 12: 8.9 -> 8.6, 15: 19.6 -> 14.8, 16: 18.6 -> 16.4, 18: 24.7 ->
 // 25.7 (the one grid that did not gain), 20: 42 -> 39, 24: 61 -> 60, 25: 240 ->
@@ -102,15 +102,17 @@ __host__ __device__ constexpr size_t pair_lds_bytes(size_t es, int n, int k, int
 }
 
 // Threads per workgroup: at least one per column; beyond that the smallest
-// workgroups that still fill the CU's wave slots from its shared memory (ns per
-// item, FP32: 18 grid 192 threads 9.8, 128 10.3; 24 grid, |k| <= 6, 192 threads
-// 20.0, 320 22.1; 27 grid 256 threads 42.6, 384 54; 36 grid 512 threads 108, 384
-// 116; FP64: 18 grid 192 threads 26.9, 128 27.4.  The 12 grid would run 64 threads
-// 5 % faster when the card is full, and loses 20 % to latency when it is not).
+// workgroups that still fill the CU's wave slots from its shared memory, FP64
+// lines, which fill them with fewer, one size up from the 18 grid on (ns per
+// item, FP32: 18 grid 128 threads 10.3 and with the split by cutoff shell 12.5,
+// 192 threads 9.8 and 12.7; 24 grid, |k| <= 6, 192 threads 20.0, 320 22.1; 27 grid
+// 256 threads 42.6, 384 54; 36 grid 512 threads 108, 384 116; FP64: 18 grid 192
+// threads 26.9, 128 27.4.  The 12 grid would run 64 threads 5 % faster when the
+// card is full, and loses 20 % to latency when it is not).
 // pair_threads has the last word: workgroups alone on their CU take 512.
-__host__ __device__ constexpr int pair_threads_shared(int n, int k) {
+__host__ __device__ constexpr int pair_threads_shared(size_t es, int n, int k) {
   const int cols = (pair_cols_max(k) + 63) / 64 * 64;
-  const int nt = n <= 16 ? 128 : n <= 24 ? 192 : n <= 27 ? 256 : 512;
+  const int nt = n <= (es == 8 ? 16 : 18) ? 128 : n <= 24 ? 192 : n <= 27 ? 256 : 512;
   return cols > nt ? cols : nt;
 }
 
@@ -144,7 +146,7 @@ __host__ __device__ constexpr int slab_fill(int n, int ns, int nt) {
 // one workgroup per CU, 170).  On the 32 grid (|k| <= 9, FP32) the exact count
 // lets one slab pass where a rounded one took two (68 -> 63 ns).
 __host__ __device__ constexpr int pair_slabs(size_t es, int n, int k, bool bins = false) {
-  const int nt = pair_threads_shared(n, k), cols = pair_cols_max(k);
+  const int nt = pair_threads_shared(es, n, k), cols = pair_cols_max(k);
   const size_t stat = pair_static(k, nt, bins);
   for (int wgs = es == 8 ? 3 : 2; wgs >= 2; --wgs)
     for (int ns = 1; ns <= n; ++ns)
@@ -161,7 +163,7 @@ __host__ __device__ constexpr int pair_slabs(size_t es, int n, int k, bool bins 
 // allow (FP64: 24 grid, |k| <= 10, 384 threads 95 ns, 512 threads 90; 25 grid 256
 // threads 125, 512 threads 101).
 __host__ __device__ constexpr int pair_threads(size_t es, int n, int k) {
-  const int nt = pair_threads_shared(n, k);
+  const int nt = pair_threads_shared(es, n, k);
   const size_t lds = pair_lds_bytes(es, n, k, pair_slabs(es, n, k), pair_cols_max(k));
   return es == 8 && lds + pair_static(k, nt, false) > size_t(80) * 1024 && nt < 512 ? 512 : nt;
 }
